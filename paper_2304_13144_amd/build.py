@@ -1,9 +1,9 @@
 """Builds libmtp.so in-tree for gfx950.
 
 Steps: compile the basis generator (g++) -> write one contraction header per
-level -> one HIP translation unit per level with the fused kernel
-instantiated for it (forward and backward, FP64 and FP32: four units per
-level) -> compile every unit with hipcc in parallel -> link.
+level -> HIP translation units per level with the kernels instantiated for
+it (moments / contraction, pair pass and, up to level 20, the backward, in
+FP64 and FP32) -> compile every unit with hipcc in parallel -> link.
 
     python -m paper_2304_13144_amd.build [--levels 8,16] [-j 8]
 """
@@ -50,7 +50,7 @@ def _run(cmd):
     return time.time() - t
 
 
-STAGE_R_PER_UNIT = 4   # reverse parts per translation unit of a staged level
+BACKWARD_MAX = 20   # the training backward is compiled up to this level
 
 
 def generate(levels):
@@ -66,13 +66,10 @@ def generate(levels):
     _run([gen_exe, tmp] + [str(L) for L in levels])
     for f in os.listdir(tmp):   # keep the mtime of unchanged programs (incremental builds)
         _write_if_changed(os.path.join(GEN, f), open(os.path.join(tmp, f)).read())
-    flops, staged = {}, {}
+    flops = {}
     for L in levels:
         txt = open(os.path.join(GEN, f"mtp_level{L}.inc")).read()
-        flops[L] = sum(int(txt.split(f"FLOPS_{k} = ")[1].split(";")[0]) for k in ("GRAPHS", "TRIE", "REVERSE"))
-        if "STAGED = true" in txt:   # (graph parts, reverse parts, graphs)
-            staged[L] = (int(txt.split("STAGE_G = ")[1].split(",")[0]), int(txt.split("STAGE_R = ")[1].split(";")[0]),
-                         int(txt.split("NGRAPH = ")[1].split(";")[0]))
+        flops[L] = int(txt.split("long FLOPS = ")[1].split(";")[0])
     units = []
 
     def unit(name, body):
@@ -82,35 +79,17 @@ def generate(levels):
 
     for L in levels:   # units per (level, arithmetic type, forward / backward): they compile in parallel
         for T, tag in (("double", "f64"), ("float", "f32")):
-            if L not in staged:
-                # moments / contraction and the pair pass in units of their own
-                # (ILP_UNITS compiles some of them differently), then the backward
-                for name, macro in ((f"efs_level{L}_{tag}_mc", "MTP_EFS_MC_LEVEL_T"),
-                                    (f"efs_level{L}_{tag}_fr", "MTP_EFS_FR_LEVEL_T"),
-                                    (f"bwd_level{L}_{tag}", "MTP_BWD_LEVEL_T")):
-                    unit(f"{name}.hip",
-                         f'#include "efs_kernel.hpp"\n#include "backward_kernel.hpp"\nnamespace mtp {{\n'
-                         f'#include "mtp_level{L}.inc"\n{macro}({L}, {T})\n}}  // namespace mtp\n')
-                continue
-            ng, nr, _ = staged[L]
-            # the staged program: moments + trie walk + pair gradients in one unit, the graph
-            # parts in one, the reverse parts in units of STAGE_R_PER_UNIT
-            decl = "".join(f"template <> void launch_graphs_stage<{L}, {T}, {q}>(const EfsArgs &a);\n" for q in range(ng))
-            decl += "".join(f"template <> void launch_reverse_stage<{L}, {T}, {q}>(const EfsArgs &a);\n" for q in range(nr))
-            unit(f"efs_level{L}_{tag}.hip",
-                 f'#include "efs_staged.hpp"\nnamespace mtp {{\n#include "mtp_level{L}.inc"\n{decl}'
-                 f'MTP_EFS_STAGED_LEVEL_T({L}, {T})\nMTP_EFS_FR_LEVEL_T({L}, {T})\n}}  // namespace mtp\n')
-            unit(f"stg_level{L}_{tag}_g.hip",
-                 f'#include "efs_staged.hpp"\nnamespace mtp {{\n#include "mtp_level{L}.inc"\n'
-                 + "".join(f'#include "mtp_level{L}_g{q}.inc"\nMTP_STAGE_G_T({L}, {T}, {q})\n' for q in range(ng))
-                 + "}  // namespace mtp\n")
-            for u in range(0, nr, STAGE_R_PER_UNIT):
-                unit(f"stg_level{L}_{tag}_r{u // STAGE_R_PER_UNIT}.hip",
-                     f'#include "efs_staged.hpp"\nnamespace mtp {{\n#include "mtp_level{L}.inc"\n'
-                     + "".join(f'#include "mtp_level{L}_r{q}.inc"\nMTP_STAGE_R_T({L}, {T}, {q})\n'
-                               for q in range(u, min(nr, u + STAGE_R_PER_UNIT)))
-                     + "}  // namespace mtp\n")
-    plain = [L for L in levels if L not in staged]
+            # moments / contraction and the pair pass in units of their own
+            # (ILP_UNITS compiles some of them differently), then the backward
+            for name, macro in ((f"efs_level{L}_{tag}_mc", "MTP_EFS_MC_LEVEL_T"),
+                                (f"efs_level{L}_{tag}_fr", "MTP_EFS_FR_LEVEL_T"),
+                                (f"bwd_level{L}_{tag}", "MTP_BWD_LEVEL_T")):
+                if macro == "MTP_BWD_LEVEL_T" and L > BACKWARD_MAX:
+                    continue
+                unit(f"{name}.hip",
+                     f'#include "efs_kernel.hpp"\n#include "backward_kernel.hpp"\nnamespace mtp {{\n'
+                     f'#include "mtp_level{L}.inc"\n{macro}({L}, {T})\n}}  // namespace mtp\n')
+    plain = [L for L in levels if L <= BACKWARD_MAX]
     decl = "".join(f"template <> int launch_mc_level_t<{L}, {T}>(const EfsArgs &a);\n"
                    f"template <> int launch_fr_level_t<{L}, {T}, {T}>(const EfsArgs &a);\n"
                    for L in levels for T in ("double", "float"))
@@ -126,7 +105,6 @@ def generate(levels):
                  for L in levels)
     bcases = "".join(f"        case {L}: return f64 ? launch_backward_level_t<{L}, double>(b) : "
                      f"launch_backward_level_t<{L}, float>(b);\n" for L in plain)
-    scases = "".join(f"        case {L}: return {staged[L][2]};\n" for L in staged)
     disp = ('#include "internal.hpp"\nnamespace mtp {\n'
             + "template <int L, typename T> int launch_mc_level_t(const EfsArgs &a);\n"
             + "template <int L, typename TF, typename TD> int launch_fr_level_t(const EfsArgs &a);\n"
@@ -139,8 +117,7 @@ def generate(levels):
             + "int launch_backward(int level, const BwdArgs &b) {\n    const bool f64 = b.e.precision == MTP_FP64;\n"
             + "    switch (level) {\n" + bcases
             + "        default: return -1;\n    }\n}\n"
-            + "int staged_graphs(int level) {\n    switch (level) {\n" + scases
-            + "        default: return 0;\n    }\n}\n"
+            + f"bool has_backward(int level) {{ return level <= {BACKWARD_MAX}; }}\n"
             + "std::vector<int> compiled_levels() { return {"
             + ", ".join(str(L) for L in levels) + "}; }\nlong contraction_flops(int level) {\n    switch (level) {\n"
             + "".join(f"        case {L}: return {flops[L]};\n" for L in levels)
@@ -169,7 +146,6 @@ def build(levels=DEFAULT_LEVELS, jobs=None, verbose=True, force=True):
     mt = os.path.getmtime
     # the per-level units see only the kernel headers and their level's program
     kernel_mtime = max(mt(d) for d in [os.path.join(CSRC, f) for f in KERNEL_HEADERS] + [os.path.abspath(__file__)])
-    staged_mtime = max(kernel_mtime, mt(os.path.join(CSRC, "efs_staged.hpp")))
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".hpp", ".h"))]
     deps += [os.path.join(os.path.dirname(HERE), "include", "mtp.h"), os.path.abspath(__file__)]
     host_mtime = max(mt(d) for d in deps)
@@ -180,9 +156,7 @@ def build(levels=DEFAULT_LEVELS, jobs=None, verbose=True, force=True):
         objs.append(obj)
         if src in units:
             level = "".join(ch for ch in os.path.basename(src).split("_")[1] if ch.isdigit())
-            progs = [f for f in os.listdir(GEN) if f == f"mtp_level{level}.inc" or f.startswith(f"mtp_level{level}_")]
-            staged_unit = any(f.startswith(f"mtp_level{level}_") for f in progs)
-            dm = max([staged_mtime if staged_unit else kernel_mtime] + [mt(os.path.join(GEN, f)) for f in progs])
+            dm = max(kernel_mtime, mt(os.path.join(GEN, f"mtp_level{level}.inc")))
         else:
             dm = host_mtime
         if force or _stale(src, obj, dm):

@@ -49,6 +49,11 @@ hipStream_t S(void *s) { return static_cast<hipStream_t>(s); }
 // k chunk of the FP64 products, which never read further)
 int ld_of(int m, int prec) { return prec == MTP_MIXED ? (m + 63) / 64 * 64 : (m + 31) / 32 * 32; }
 
+// column stride of the rows of n neighborhoods: whole blocks of 64 (the
+// contraction writes whole columns of its block, and every column starts at
+// a cache line)
+int64_t ldn_of(int64_t n) { return (n + 63) / 64 * 64; }
+
 // FULL-mode gauge: per mu drop mu+1 columns of block c_mu chosen as the
 // first mu+1 pivots of a column-pivoted Gram-Schmidt (= QR with column
 // pivoting) of the (mu+1) x (T^2 N_polyn) matrix [c_0; ...; c_mu].
@@ -258,7 +263,7 @@ void evaluate(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb, int p
     double *site = o.site_e;
     if (want_e && !site) site = static_cast<double *>(ws.get(m->sitebuf, sizeof(double) * (size_t)std::max<int64_t>(1, n)));
     double *brow = want_rows ? static_cast<double *>(ws.get(m->brow, sizeof(double) * (size_t)ldb *
-                                                                        (size_t)std::max<int64_t>(1, n)))
+                                                                        (size_t)std::max<int64_t>(1, ldn_of(n))))
                              : nullptr;
     if (n == 0) {
         if (o.energy) launch_zero(o.energy, sizeof(double) * s->n_cfg, st);
@@ -285,7 +290,7 @@ void evaluate(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb, int p
     a.F = o.forces;
     a.virial = virial;
     a.brow = brow;
-    a.ldn = n;
+    a.ldn = ldn_of(n);
     a.ldb = ldb;
     a.grade_mode = o.mode;
     a.colmap = m->colmap.as<int32_t>();
@@ -297,11 +302,6 @@ void evaluate(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb, int p
     a.stream = st;
     a.mbuf = ws.get(m->mbuf, msz * m->basis.n_comp() * (size_t)n);
     a.dmbuf = ws.get(m->dmbuf, msz * m->basis.n_comp() * (size_t)n);
-    if (const int ngs = staged_graphs(m->level)) {   // tiles of 64 neighborhoods
-        const size_t bytes = msz * ngs * (size_t)((n + 63) / 64 * 64);
-        a.gval = ws.get(m->gval, bytes);
-        a.dgval = ws.get(m->dgval, bytes);
-    }
     // per-configuration sums: chunk partials, then one block per configuration.
     // With forces and a preselection the force gather runs as extra blocks of
     // the preselection's launch (one launch less per step) and the partials
@@ -344,7 +344,7 @@ void evaluate(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb, int p
                 ws.get(m->selblk, sizeof(int32_t) * (size_t)((n + count_rows - 1) / count_rows + 1)));
         {
             ProfScope ps("grade", st);
-            launch_grade(m->act[o.mode], prec, brow, ldb, n, n, gam, o.argmax, st, o.sel_thr, blk, sched);
+            launch_grade(m->act[o.mode], prec, brow, ldb, a.ldn, n, gam, o.argmax, st, o.sel_thr, blk, sched);
         }
         if (want_sel) {
             ProfScope ps("select", st);
@@ -353,7 +353,7 @@ void evaluate(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb, int p
                                 want_sums ? &csums : nullptr, fuse_gather ? &ga : nullptr, count_rows);
         }
     }
-    if (o.b_rows) launch_copy_rows(brow, n, mm, n, static_cast<double *>(o.b_rows), st);
+    if (o.b_rows) launch_copy_rows(brow, a.ldn, mm, n, static_cast<double *>(o.b_rows), st);
     MTP_HIP(hipGetLastError());
 }
 
@@ -747,7 +747,7 @@ int mtp_grade_cfg(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb, m
         launch_zero(m->cfgrows.ptr, sizeof(double) * (size_t)ldb * s->n_cfg, st);
     } else {
         ProfScope ps("cfg_rows", st);
-        launch_cfg_rows(m->brow.as<double>(), ldb, n, s, m->cfgpart.as<double>(), m->cfgrows.as<double>(), st);
+        launch_cfg_rows(m->brow.as<double>(), ldn_of(n), ldb, n, s, m->cfgpart.as<double>(), m->cfgrows.as<double>(), st);
     }
     if (want_grade) {
         m->gamma_ws.ensure(sizeof(double) * s->n_cfg);
@@ -812,7 +812,7 @@ int mtp_b_rows(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb, mtp_
     MTP_HIP(hipSetDevice(m->device));
     const int mm = m->m_of(g);
     const int ldb = ld_of(mm, MTP_FP64);
-    m->brow.ensure(sizeof(double) * (size_t)ldb * n_idx);
+    m->brow.ensure(sizeof(double) * (size_t)ldb * (size_t)ldn_of(n_idx));
     EfsArgs a{};
     a.n_atoms = n_idx;
     a.atom_list = idx;
@@ -827,7 +827,7 @@ int mtp_b_rows(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb, mtp_
     a.th32 = m->theta32.as<float>();
     a.n_lin = m->basis.n_lin();
     a.brow = m->brow.as<double>();
-    a.ldn = n_idx;
+    a.ldn = ldn_of(n_idx);
     a.ldb = ldb;
     a.grade_mode = g;
     a.colmap = m->colmap.as<int32_t>();
@@ -840,16 +840,9 @@ int mtp_b_rows(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb, mtp_
     m->dmbuf.ensure(sizeof(double) * m->basis.n_comp() * (size_t)n_idx);
     a.mbuf = m->mbuf.ptr;
     a.dmbuf = m->dmbuf.ptr;
-    if (const int ngs = staged_graphs(m->level)) {
-        const size_t bytes = sizeof(double) * ngs * (size_t)((n_idx + 63) / 64 * 64);
-        m->gval.ensure(bytes);
-        m->dgval.ensure(bytes);
-        a.gval = m->gval.ptr;
-        a.dgval = m->dgval.ptr;
-    }
     int e = launch_efs(m->level, a);
     MTP_CHECK(e == 0, MTP_E_HIP, std::string("efs kernel launch: ") + hipGetErrorString((hipError_t)e));
-    launch_copy_rows(m->brow.as<double>(), n_idx, mm, n_idx, rows, S(stream));
+    launch_copy_rows(m->brow.as<double>(), a.ldn, mm, n_idx, rows, S(stream));
     API_END
 }
 
@@ -1257,9 +1250,9 @@ int mtp_efs_backward(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb
     check_system(m, s);
     check_nbrs(m, s, nb);
     MTP_CHECK(p == MTP_FP64 || p == MTP_MIXED, MTP_E_INVAL, "bad precision");
-    MTP_CHECK(!staged_graphs(m->level), MTP_E_UNSUPPORTED,
-              "level " + std::to_string(m->level) + " is compiled as a staged program, which evaluates energies, "
-              "forces, stresses and rows; its backward pass is not built");
+    MTP_CHECK(has_backward(m->level), MTP_E_UNSUPPORTED,
+              "level " + std::to_string(m->level) + ": energies, forces, stresses and rows only; its backward pass is "
+              "not built");
     MTP_HIP(hipSetDevice(m->device));
     hipStream_t st = S(stream);
     const int64_t n = s->n_atoms;
@@ -1269,11 +1262,9 @@ int mtp_efs_backward(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb
     }
     const size_t tsz = p == MTP_FP64 ? sizeof(double) : sizeof(float);
     const size_t nc = m->basis.n_comp();
-    m->mbuf.ensure(tsz * nc * n);
     m->dmbuf.ensure(tsz * nc * n);
-    m->tbuf.ensure(tsz * nc * n);
     m->dtbuf.ensure(tsz * nc * n);
-    m->rows.ensure(tsz * (size_t)m->n_theta * n);
+    m->rows.ensure(tsz * (size_t)(m->basis.n_lin() + m->n_types * m->basis.n_rad * NPOLY) * (size_t)ldn_of(n));
     BwdArgs b{};
     EfsArgs &a = b.e;
     a.n_atoms = n;
@@ -1289,20 +1280,16 @@ int mtp_efs_backward(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb
     a.th32 = m->theta32.as<float>();
     a.n_lin = m->basis.n_lin();
     a.precision = p;
-    a.lanes = 4;
-    a.lanes_mc = 4;
+    a.ldn = ldn_of(n);
     a.stream = st;
-    a.mbuf = m->mbuf.ptr;
     a.dmbuf = m->dmbuf.ptr;
     b.gE = gE;
     b.gF = gF;
     b.gS = gS;
     b.atom_cfg = nb->atom_cfg.as<int32_t>();
     b.nbr_j = nb->j.as<int32_t>();
-    b.tbuf = m->tbuf.ptr;
     b.dtbuf = m->dtbuf.ptr;
-    b.rows = m->rows.ptr;
-    b.n_theta = m->n_theta;
+    b.cols = m->rows.ptr;
     int e;
     {
         ProfScope ps("backward", st);
@@ -1311,7 +1298,8 @@ int mtp_efs_backward(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb
     MTP_CHECK(e == 0, MTP_E_HIP, std::string("backward kernel launch: ") + hipGetErrorString((hipError_t)e));
     {
         ProfScope ps("backward_sum", st);
-        launch_column_sums(m->rows.ptr, p, n, m->n_theta, g_theta, st, m->sums);
+        launch_theta_sums(m->rows.ptr, p, a.ldn, n, m->basis.n_lin(), m->basis.n_rad, m->n_types, s->type, gE,
+                          nb->atom_cfg.as<int32_t>(), g_theta, st, m->sums);
     }
     MTP_HIP(hipGetLastError());
     API_END
@@ -1396,12 +1384,12 @@ int mtp_tune(mtp_model *m, const mtp_system *s, const mtp_nbrs *nb, mtp_precisio
         constexpr int GREPS = 10;
         try {
             for (int sc : cand)
-                launch_grade(m->act[g], p, rows, ldb, n, n, o.gamma, nullptr, st, 2.0, blk.as<int32_t>(), sc);
+                launch_grade(m->act[g], p, rows, ldb, ldn_of(n), n, o.gamma, nullptr, st, 2.0, blk.as<int32_t>(), sc);
             for (int rd = 0; rd < ROUNDS; ++rd)
                 for (size_t k = 0; k < cand.size(); ++k) {
                     MTP_HIP(hipEventRecord(e0, st));
                     for (int r = 0; r < GREPS; ++r)
-                        launch_grade(m->act[g], p, rows, ldb, n, n, o.gamma, nullptr, st, 2.0, blk.as<int32_t>(),
+                        launch_grade(m->act[g], p, rows, ldb, ldn_of(n), n, o.gamma, nullptr, st, 2.0, blk.as<int32_t>(),
                                      cand[k]);
                     MTP_HIP(hipEventRecord(e1, st));
                     MTP_HIP(hipEventSynchronize(e1));

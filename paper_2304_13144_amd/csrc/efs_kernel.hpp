@@ -23,6 +23,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <utility>
+
 #include "device_util.hpp"
 #include "kernel_args.hpp"
 
@@ -223,40 +225,30 @@ __global__ __launch_bounds__(256) void efs_moments(const EfsArgs a) {
 }
 
 // ---- kernel 2: contraction, site energy (eq. 2), dV/dM -------------------
-// One block holds 64 neighborhoods (one per lane) and four (or eight)
-// wavefronts; the graphs of the contraction program are split into four and
-// into eight parts at build time (Level<L>::graph_part, graph_part8).
-// Wavefront w evaluates the graph values of part w, all exchange them through
-// LDS, each runs the (short) trie walk for V, B_alpha and dV/dg, and
-// wavefront w runs the reverse pass of part w.  The partial dV/dM are added
-// in LDS in a fixed order.
+// One block holds 64 neighborhoods (one per lane) and NW = four or eight
+// wavefronts that share the contraction program.  FP64 (and FP32 above level
+// 16) runs the factorised program (fact_body), FP32 up to level 16 the
+// expanded one (expanded_body).
 template <typename T> struct ColLoad {   // component k of one neighborhood, [k][n] layout
     const T *p;
     int64_t s;
     __device__ T operator[](int k) const { return p[k * s]; }
 };
-template <typename T> struct LdsSink {   // receives B_alpha into [alpha][64] in LDS
-    T *p;
-    __device__ T &operator[](int k) const { return p[k * 64]; }
-};
-// receives B_alpha straight into column c0 + alpha of the FP64 rows (when
-// staging them would not fit in LDS): a uniform column base plus the lane's
-// row index, consecutive lanes writing consecutive words
+// receives B_alpha into column c0 + alpha of the FP64 rows: a uniform column
+// base plus the lane's row index, consecutive lanes writing consecutive words
+// (columns are padded to whole blocks of 64 rows: lanes past the last
+// neighborhood write the padding, without a branch around every store)
 struct ColSink {
     double *p;
     int64_t s;
     int c0;
     uint32_t row;
-    bool on;
     struct Ref {
         double *col;
         uint32_t row;
-        bool on;
-        __device__ void operator=(const double &v) const {
-            if (on) col[row] = v;
-        }
+        __device__ void operator=(const double &v) const { col[row] = v; }
     };
-    __device__ Ref operator[](int k) const { return Ref{p + (int64_t)(c0 + k) * s, row, on}; }
+    __device__ Ref operator[](int k) const { return Ref{p + (int64_t)(c0 + k) * s, row}; }
 };
 struct NoSink {
     struct Ref {
@@ -270,54 +262,201 @@ template <typename T> struct LdsCol {   // component k of one neighborhood, [k][
     __device__ T operator[](int k) const { return p[k * 64]; }
 };
 
-// Rows of graph values / B_alpha staged in LDS: the graph values, and with
-// rows wanted (WB) B_alpha in the same place once the graph values are read,
-// when that fits in STAGE_BYTES (else B_alpha goes straight to memory).
-constexpr int STAGE_BYTES = 64 * 1024;
-template <typename T, int L, bool WB> constexpr bool stage_b() {
-    return WB && Level<L>::NLIN * 64 * (int)sizeof(T) <= STAGE_BYTES;
-}
-template <typename T, int L, bool WB> constexpr int sg_rows() {
-    return stage_b<T, L, WB>() && Level<L>::NLIN > Level<L>::NGRAPH ? Level<L>::NLIN : Level<L>::NGRAPH;
+// products with constants and coefficients (which carry no tangent when the
+// program runs on dual numbers)
+__device__ inline double cmul(double c, double x) { return c * x; }
+__device__ inline float cmul(float c, float x) { return c * x; }
+__device__ inline double cfma(double c, double x, double y) { return fma(c, x, y); }
+__device__ inline float cfma(float c, float x, float y) { return fma(c, x, y); }
+
+// between the graphs of a cluster: no instruction is scheduled across, so
+// that the graphs are not interleaved, which would hold the intermediates of
+// many at once
+#define MTP_FACT_SCHED() __builtin_amdgcn_sched_barrier(0)
+
+template <typename T, int L> constexpr bool expanded_program() {
+    return sizeof(T) == sizeof(float) && Level<L>::EXPANDED;
 }
 
-// The contraction of the 64 neighborhoods of block blk (a block of NW = 4
-// or 8 wavefronts), the moments read through M; sg, sdm: LDS scratch.
-// ALIAS: sdm shares its storage with the moments M (they are dead once every
-// wavefront has finished its reverse part, which a barrier makes sure of).
-// WB: B_alpha goes into the rows (FP64 only: rows are always FP64), staged
-// in sg and written column by column (64 consecutive rows per store).
-template <typename T, int L, bool WB, typename MA, int NW = 4, bool ALIAS = false>
-__device__ inline void contract_body(const EfsArgs &a, int64_t blk, const MA &M,
-                                     T (&sg)[sg_rows<T, L, WB>()][64], T (&sdm)[Level<L>::NC][64]) {
+// The clusters of the factorised program for NW wavefronts.
+template <int L, int NW> struct Fact {
+    using LV = Level<L>;
+    static_assert(NW == 4 || NW == 8, "four or eight clusters");
+    static constexpr int MAXC = NW == 4 ? LV::FMAX4 : LV::FMAX8;
+    static constexpr int ROWS = LV::NC + LV::NPROD;          // dV/dM, then the sums X_p
+    static constexpr int SLICE = (ROWS + NW - 1) / NW;
+    static constexpr int ncomp(int P) {
+        if constexpr (NW == 4) return LV::fncomp4[P];
+        else return LV::fncomp8[P];
+    }
+    static constexpr int comp(int P, int i) {
+        if constexpr (NW == 4) return LV::fcomp4[P][i];
+        else return LV::fcomp8[P][i];
+    }
+    // position of sum k in cluster P's list, or -1
+    static constexpr int find(int P, int k) {
+        for (int i = 0; i < ncomp(P); ++i)
+            if (comp(P, i) == k) return i;
+        return -1;
+    }
+    static constexpr bool is_low(int k) {
+        for (int i = 0; i < LV::NLOWC; ++i)
+            if (LV::low_comp[i] == k) return true;
+        return false;
+    }
+    // Everything below is unrolled by index sequences, not loops: d must be
+    // addressed by constants from the start to stay in registers.
+    // cluster P's share of sum k (SET: the first to reach it)
+    template <int P, int k, bool SET, typename T>
+    static __device__ __forceinline__ void add_one(const T (&d)[MAXC], T (*sum)[64], int lane) {
+        if constexpr (k < ROWS) {
+            constexpr int i = find(P, k);
+            if constexpr (SET) sum[k][lane] = i >= 0 ? d[i < 0 ? 0 : i] : T(0);
+            else if constexpr (i >= 0) sum[k][lane] = sum[k][lane] + d[i];
+        }
+    }
+    template <int P, int Q, bool SET, typename T, int... I>
+    static __device__ __forceinline__ void add(const T (&d)[MAXC], T (*sum)[64], int lane,
+                                               std::integer_sequence<int, I...>) {
+        (add_one<P, Q * SLICE + I, SET>(d, sum, lane), ...);
+    }
+    template <int P, bool WB, typename T, typename MP, typename XP, typename BP>
+    static __device__ __forceinline__ void cluster(const MP &M, const T (&p)[LV::NPROD], const XP &xi, const BP &sink,
+                                                   T (&d)[MAXC]) {
+        if constexpr (NW == 4) LV::template fact4<P, WB>(M, p, xi, sink, d);
+        else LV::template fact8<P, WB>(M, p, xi, sink, d);
+    }
+    // the last wavefront's end: dV/dM of the low components, written out
+    template <typename T, typename OUT, int... I>
+    static __device__ __forceinline__ void low_out(const T *d, T (*sum)[64], int lane, const OUT &out,
+                                                   std::integer_sequence<int, I...>) {
+        (out(LV::low_comp[I], sum[LV::low_comp[I]][lane] + d[I]), ...);
+    }
+};
+
+// The code of this wavefront's cluster P, inside a function whose own arrays
+// it uses: written out as a switch there, since a helper holding the branches
+// is simplified by itself first, where stores to a caller's array merge under
+// a selected address and the array ends in scratch memory.
+#define MTP_WAVE_CASE(Q, ...)                    \
+    case Q:                                      \
+        if constexpr (Q < NW) {                  \
+            constexpr int P = Q;                 \
+            __VA_ARGS__;                         \
+        }                                        \
+        break;
+#define MTP_BY_WAVE(...)                         \
+    switch (wave) {                              \
+        MTP_WAVE_CASE(0, __VA_ARGS__)            \
+        MTP_WAVE_CASE(1, __VA_ARGS__)            \
+        MTP_WAVE_CASE(2, __VA_ARGS__)            \
+        MTP_WAVE_CASE(3, __VA_ARGS__)            \
+        MTP_WAVE_CASE(4, __VA_ARGS__)            \
+        MTP_WAVE_CASE(5, __VA_ARGS__)            \
+        MTP_WAVE_CASE(6, __VA_ARGS__)            \
+        MTP_WAVE_CASE(7, __VA_ARGS__)            \
+    }
+// step S of the reduction: wavefront P adds slice (P + S) % NW, so every
+// wavefront works on a slice of its own and each sum has a fixed order
+#define MTP_REDUCE_STEP(S)                                                                                       \
+    if constexpr (S < NW) {                                                                                      \
+        MTP_BY_WAVE(FA::template add<P, (P + S) % NW, S == 0>(d, sum, lane,                                      \
+                                                              std::make_integer_sequence<int, FA::SLICE>{}))     \
+        __syncthreads();                                                                                         \
+    }
+
+// The factorised contraction of one block's 64 neighborhoods: wavefront w
+// runs cluster w forward and back on the moments M, the last one the low
+// graphs besides; the shares of dV/dM and of the sums X_p are added in LDS
+// (sum), every wavefront on a slice of its own per step; then the last
+// wavefront closes the low graphs with the X_p while the others write dV/dM.
+// out(k, v): component k of dV/dM; site(V): the site energy (last wavefront).
+// No graph value passes between wavefronts and the trie walk is not repeated
+// by each, as in the expanded form.  Bound by FP64 issue at two wavefronts per
+// SIMD (256 VGPRs hold a cluster's sums and intermediates).  Level 24, 160
+// configurations, 76,930 atoms (energies, forces, stress): 1,539 us with the
+// expanded program in 25 launches through memory, 396 us in this one launch;
+// level 16, 16,384 atoms with rows: 27.8 -> 22.3 us for this launch.
+template <typename T, int L, bool WB, int NW, typename MP, typename XP, typename BP, typename OUT, typename SITE>
+__device__ __forceinline__ void fact_body(const MP &M, const XP &xi, const BP &sink, T (*sum)[64], const OUT &out,
+                                          const SITE &site) {
+    using LV = Level<L>;
+    using FA = Fact<L, NW>;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    constexpr int NLA = LV::NLOW > 0 ? LV::NLOW : 1, NCA = LV::NLOWC > 0 ? LV::NLOWC : 1;
+    T gl[NLA], p[LV::NPROD], dz[NLA], V = T(0);
+    p[0] = T(1);
+    if constexpr (LV::NLOW > 0) LV::template low_values<T>(M, gl, p);
+    {
+        T d[FA::MAXC];
+        MTP_BY_WAVE(FA::template cluster<P, WB>(M, p, xi, sink, d))
+        if (wave == NW - 1) LV::template low_functions<WB>(gl, xi, sink, dz, V);
+        MTP_REDUCE_STEP(0)
+        MTP_REDUCE_STEP(1)
+        MTP_REDUCE_STEP(2)
+        MTP_REDUCE_STEP(3)
+        MTP_REDUCE_STEP(4)
+        MTP_REDUCE_STEP(5)
+        MTP_REDUCE_STEP(6)
+        MTP_REDUCE_STEP(7)
+    }
+    if (wave == NW - 1) {
+        T X[LV::NPROD], d[NCA];
+#pragma unroll
+        for (int q = 0; q < LV::NPROD; ++q) X[q] = sum[LV::NC + q][lane];
+        LV::template low_coupling<T>(gl, p, X, dz, V);
+        if constexpr (LV::NLOW > 0) {
+            LV::template low_reverse<T>(M, dz, d);
+            FA::low_out(d, sum, lane, out, std::make_integer_sequence<int, LV::NLOWC>{});
+        }
+        site(V);
+    } else {
+        for (int k = wave; k < LV::NC; k += NW - 1)
+            if (!FA::is_low(k)) out(k, sum[k][lane]);
+    }
+}
+
+// the rows' constant entries, in whole columns of 64 rows: the species
+// one-hot, then zeros from column nt + NL on (the c part's blocks and the
+// padding; the pair pass writes the neighborhood's own c block over them
+// afterwards).  Issued first, so that they drain while the graph values are
+// computed (no vector memory load follows that would wait for them)
+template <int L, int NW> __device__ inline void constant_columns(const EfsArgs &a, int64_t slot, int wave) {
+    if (slot >= a.n_atoms) return;
+    const int nt = a.n_types;
+    const int64_t atom = a.atom_list ? (int64_t)a.atom_list[slot] : slot;
+    int zi = a.type[atom];
+    zi = zi < 0 ? 0 : (zi >= nt ? nt - 1 : zi);
+    double *rowp = a.brow + slot;
+    const int c0 = nt + Level<L>::NLIN;
+    for (int k = wave; k < nt + a.ldb - c0; k += NW) {
+        const int col = k < nt ? k : c0 + (k - nt);
+        rowp[(int64_t)col * a.ldn] = k == zi ? 1.0 : 0.0;
+    }
+}
+
+// V + xi_0[z_i] of slot's atom
+template <typename T> __device__ inline void write_site(const EfsArgs &a, int64_t slot, T V) {
+    if (slot >= a.n_atoms || !a.site_e) return;
+    const int nt = a.n_types;
+    const int64_t atom = a.atom_list ? (int64_t)a.atom_list[slot] : slot;
+    int zi = a.type[atom];
+    zi = zi < 0 ? 0 : (zi >= nt ? nt - 1 : zi);
+    a.site_e[atom] = double(V) + double(xi0_of<T>(a)[zi]);
+}
+
+// The expanded contraction (FP32): the graphs are split into NW parts;
+// wavefront w evaluates the graph values of part w, all exchange them through
+// LDS (sg), each runs the (short) trie walk for V and dV/dg, and wavefront w
+// the reverse pass of part w.  The partial dV/dM are added in LDS (sdm) in a
+// fixed order.  ALIAS: sdm shares its storage with the moments M.
+template <typename T, int L, typename MA, int NW, bool ALIAS>
+__device__ inline void expanded_body(const EfsArgs &a, int64_t blk, const MA &M, T (*sg)[64], T (*sdm)[64]) {
     using LV = Level<L>;
     constexpr int NC = LV::NC, NG = LV::NGRAPH;
     static_assert(LV::NPART == 4 && LV::NPART8 == 8 && (NW == 4 || NW == 8), "four or eight parts");
-    static_assert(!WB || sizeof(T) == sizeof(double), "rows are FP64");
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t slot = blk * 64 + lane;
-    const bool live = slot < a.n_atoms;
-    const int64_t sl = live ? slot : 0;
-    if constexpr (WB) {
-        // the rows' constant entries, in whole columns of 64 rows: the species
-        // one-hot, then zeros from column nt + NL on (the c part's blocks and
-        // the padding; the pair pass writes the neighborhood's own c block
-        // over them afterwards).  Issued first, so that they drain while the
-        // graph values are computed (no vector memory load follows that
-        // would wait for them)
-        if (live) {
-            const int ntp = a.n_types;
-            const int64_t atom = a.atom_list ? (int64_t)a.atom_list[slot] : slot;
-            int zi = a.type[atom];
-            zi = zi < 0 ? 0 : (zi >= ntp ? ntp - 1 : zi);
-            double *rowp = a.brow + sl;
-            const int c0 = ntp + LV::NLIN;
-            for (int k = wave; k < ntp + a.ldb - c0; k += NW) {
-                const int col = k < ntp ? k : c0 + (k - ntp);
-                rowp[(int64_t)col * a.ldn] = k == zi ? 1.0 : 0.0;
-            }
-        }
-    }
     {
         T g[NG];
         if constexpr (NW == 4) {
@@ -348,24 +487,8 @@ __device__ inline void contract_body(const EfsArgs &a, int64_t blk, const MA &M,
 #pragma unroll
     for (int G = 0; G < NG; ++G) gin[G] = sg[G][lane];
     T V = T(0);
-    const int nt = a.n_types;
     const XiPtr<T> xi{xi_of<T>(a)};
-    if constexpr (stage_b<T, L, WB>()) {
-        __syncthreads();   // every wavefront has read the graph values: sg takes B_alpha
-        if (wave == 0) {
-            LV::template trie<T, true>(gin, xi, LdsSink<T>{&sg[0][lane]}, dg, V);
-        } else {
-            LV::template trie<T, false>(gin, xi, NoSink{}, dg, V);
-        }
-    } else if constexpr (WB) {
-        if (wave == 0) {
-            LV::template trie<T, true>(gin, xi, ColSink{a.brow, a.ldn, nt, (uint32_t)sl, live}, dg, V);
-        } else {
-            LV::template trie<T, false>(gin, xi, NoSink{}, dg, V);
-        }
-    } else {
-        LV::template trie<T, false>(gin, xi, NoSink{}, dg, V);
-    }
+    LV::template trie<T, false>(gin, xi, NoSink{}, dg, V);
     T dMp[NC];
     if constexpr (NW == 4) {
         switch (wave) {
@@ -394,88 +517,95 @@ __device__ inline void contract_body(const EfsArgs &a, int64_t blk, const MA &M,
         }
         __syncthreads();
     }
-    if constexpr (stage_b<T, L, WB>()) {   // B_alpha (written to sg by wavefront 0 before the barriers above)
-        double *col = a.brow + (int64_t)nt * a.ldn + sl;
-        if (live)
-            for (int k = wave; k < LV::NLIN; k += NW) col[(int64_t)k * a.ldn] = sg[k][lane];
-    }
-    if (live) {
+    if (slot < a.n_atoms) {
         T *dout = static_cast<T *>(a.dmbuf);
         for (int k = wave; k < NC; k += NW) dout[(int64_t)k * a.n_atoms + slot] = sdm[k][lane];
-        if (wave == 0 && a.site_e) {
-            const int64_t atom = a.atom_list ? (int64_t)a.atom_list[slot] : slot;
-            int zi = a.type[atom];
-            zi = zi < 0 ? 0 : (zi >= nt ? nt - 1 : zi);
-            a.site_e[atom] = double(V) + double(xi0_of<T>(a)[zi]);
-        }
+        if (wave == 0) write_site<T>(a, slot, V);
     }
 }
 
+// rows of LDS scratch the contraction needs besides the moments
+template <typename T, int L, int NW> constexpr int scratch_rows() {
+    if constexpr (expanded_program<T, L>()) return Level<L>::NGRAPH;
+    else return Fact<L, NW>::ROWS;
+}
+
+// The contraction of the 64 neighborhoods of block blk, the moments read
+// through M.  sM: the moments' LDS, or NULL when they are in memory.
+template <typename T, int L, bool WB, int NW, typename MA>
+__device__ __forceinline__ void contract_body(const EfsArgs &a, int64_t blk, const MA &M, T (*scratch)[64], T (*sM)[64]) {
+    static_assert(!WB || sizeof(T) == sizeof(double), "rows are FP64");
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int64_t slot = blk * 64 + lane;
+    const bool live = slot < a.n_atoms;
+    if constexpr (WB) constant_columns<L, NW>(a, slot, wave);
+    if constexpr (expanded_program<T, L>()) {
+        expanded_body<T, L, MA, NW, true>(a, blk, M, scratch, sM);
+    } else {
+        T *dout = static_cast<T *>(a.dmbuf) + slot;
+        const auto out = [&](int k, T v) {
+            if (live) dout[(int64_t)k * a.n_atoms] = v;
+        };
+        const auto site = [&](T V) { write_site<T>(a, slot, V); };
+        const XiPtr<T> xi{xi_of<T>(a)};
+        if constexpr (WB)
+            fact_body<T, L, true, NW>(M, xi, ColSink{a.brow, a.ldn, a.n_types, (uint32_t)slot}, scratch, out, site);
+        else
+            fact_body<T, L, false, NW>(M, xi, NoSink{}, scratch, out, site);
+    }
+}
+
+// wavefronts of the contraction when the moments come through memory: four
+// clusters, or eight where a quarter of the graphs is more than a wavefront's
+// registers hold (level 24: 60 components and 150 intermediates); there the
+// fused launch comes with eight lanes only
+template <int L> constexpr int contract_waves() { return Level<L>::NGRAPH <= 128 ? 4 : 8; }
+
 template <typename T, int L, bool WB>
-__global__ __launch_bounds__(256) void efs_contract(const EfsArgs a) {
+__global__ __launch_bounds__(64 * contract_waves<L>()) void efs_contract(const EfsArgs a) {
     using LV = Level<L>;
-    __shared__ T sg[sg_rows<T, L, WB>()][64];
-    __shared__ T sdm[LV::NC][64];
+    constexpr int NW = contract_waves<L>();
+    __shared__ T scratch[scratch_rows<T, L, NW>()][64];
+    __shared__ T sdm[expanded_program<T, L>() ? LV::NC : 1][64];
     const int64_t slot = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
     const int64_t sl = slot < a.n_atoms ? slot : 0;
-    contract_body<T, L, WB>(a, blockIdx.x, ColLoad<T>{static_cast<const T *>(a.mbuf) + sl, a.n_atoms}, sg, sdm);
+    contract_body<T, L, WB, NW>(a, blockIdx.x, ColLoad<T>{static_cast<const T *>(a.mbuf) + sl, a.n_atoms}, scratch, sdm);
 }
 
-// Kernels 1 and 2 in one launch (four lanes per neighborhood: the 256
-// threads of a block hold the same 64 neighborhoods in both phases): the
-// reduce-scattered moments go to LDS instead of memory, and after one
-// barrier the contraction reads them there.  dV/dM reuses the moments'
-// LDS and B_alpha the graph values', so a block holds the radial
-// coefficients, the moments and max(graph values, B_alpha) only (78 KB at
-// level 16 in FP64 with rows, 45 KB without: two blocks per CU).
+// Kernels 1 and 2 in one launch, K = NW = four or eight lanes per
+// neighborhood (the block's threads hold the same 64 neighborhoods in both
+// phases): the reduce-scattered moments go to LDS instead of memory, and
+// after one barrier the contraction reads them there.
+template <typename T, int L, bool WB, int K>
+__device__ __forceinline__ void moments_contract(const EfsArgs &a) {
+    using LV = Level<L>;
+    constexpr int NC = LV::NC, NR = LV::NRAD;
+    constexpr int NCP = (NC + K - 1) / K * K;
+    __shared__ T c_s[NR * MAX_TYPES * MAX_TYPES * NPOLY];
+    __shared__ T sM[NCP][64];
+    __shared__ T scratch[scratch_rows<T, L, K>()][64];
+    load_coefs<T, NR, 64 * K>(a, c_s);
+    const int sub = threadIdx.x % K;
+    const AtomCtx c = atom_ctx<K, 64 * K>(a);
+    {
+        T M[NCP];
+        moments_scattered<T, L, K>(a, c, c_s, M);
+        const int la = threadIdx.x / K;
+#pragma unroll
+        for (int i = 0; i < NCP / K; ++i) sM[sub * (NCP / K) + i][la] = M[i];
+    }
+    __syncthreads();
+    contract_body<T, L, WB, K>(a, blockIdx.x, LdsCol<T>{&sM[0][threadIdx.x & 63]}, scratch, sM);
+}
+
 template <typename T, int L, bool WB>
 __global__ __launch_bounds__(256) void efs_moments_contract(const EfsArgs a) {
-    using LV = Level<L>;
-    constexpr int K = 4, NC = LV::NC, NR = LV::NRAD;
-    constexpr int NCP = (NC + K - 1) / K * K;
-    __shared__ T c_s[NR * MAX_TYPES * MAX_TYPES * NPOLY];
-    __shared__ T sM[NCP][64];
-    __shared__ T sg[sg_rows<T, L, WB>()][64];
-    load_coefs<T, NR>(a, c_s);
-    const int sub = threadIdx.x % K;
-    const AtomCtx c = atom_ctx<K>(a);
-    {
-        T M[NCP];
-        moments_scattered<T, L, K>(a, c, c_s, M);
-        const int la = threadIdx.x / K;
-#pragma unroll
-        for (int i = 0; i < NCP / K; ++i) sM[sub * (NCP / K) + i][la] = M[i];
-    }
-    __syncthreads();
-    contract_body<T, L, WB, LdsCol<T>, 4, true>(a, blockIdx.x, LdsCol<T>{&sM[0][threadIdx.x & 63]}, sg,
-                                                 reinterpret_cast<T (&)[NC][64]>(sM));
+    moments_contract<T, L, WB, 4>(a);
 }
 
-// The same with eight wavefronts (512 threads, eight lanes per neighborhood
-// for the moments) and the eight-part contraction program: 64 neighborhoods
-// per block as before, but two wavefronts per SIMD instead of one while the
-// straight-line contraction runs.
 template <typename T, int L, bool WB>
 __global__ __launch_bounds__(512) void efs_moments_contract8(const EfsArgs a) {
-    using LV = Level<L>;
-    constexpr int K = 8, NC = LV::NC, NR = LV::NRAD;
-    constexpr int NCP = (NC + K - 1) / K * K;
-    __shared__ T c_s[NR * MAX_TYPES * MAX_TYPES * NPOLY];
-    __shared__ T sM[NCP][64];
-    __shared__ T sg[sg_rows<T, L, WB>()][64];
-    load_coefs<T, NR, 512>(a, c_s);
-    const int sub = threadIdx.x % K;
-    const AtomCtx c = atom_ctx<K, 512>(a);
-    {
-        T M[NCP];
-        moments_scattered<T, L, K>(a, c, c_s, M);
-        const int la = threadIdx.x / K;
-#pragma unroll
-        for (int i = 0; i < NCP / K; ++i) sM[sub * (NCP / K) + i][la] = M[i];
-    }
-    __syncthreads();
-    contract_body<T, L, WB, LdsCol<T>, 8, true>(a, blockIdx.x, LdsCol<T>{&sM[0][threadIdx.x & 63]}, sg,
-                                                 reinterpret_cast<T (&)[NC][64]>(sM));
+    moments_contract<T, L, WB, 8>(a);
 }
 
 // Chebyshev values (and derivatives) at u for the radial basis (eq. 4)
@@ -522,10 +652,9 @@ __device__ inline void load_dm(const EfsArgs &a, const AtomCtx &c, int sub, T (&
 // work, Sec. II.C) -- R = 2 (FULL) the radial-coefficient part
 // dV_i/dc_{mu, z_i, z_j, beta} = sum_j T_beta(r_ij) (R_cut - r_ij)^2 P_mu(r_ij)
 // from the P_mu and Chebyshev values the gradient already has (32 more FMAs
-// per pair at N_rad = 4), then for R = 1 and 2 the species one-hot and the
-// zero padding.  The same sums in the same order as kernel 4 at the same
-// lanes, so the rows are the same bit for bit.  s_col: the kept-column map
-// (R = 2).
+// per pair at N_rad = 4); the constant columns come from the contraction.
+// The same sums in the same order as kernel 4 at the same lanes, so the rows
+// are the same bit for bit.  s_col: the kept-column map (R = 2).
 template <typename T, int L, int K, bool G, typename TD = T, int R = 0>
 __device__ inline void efs_forces_body(const EfsArgs &a, int64_t blk, T *c_s, T (&s_dm)[Level<L>::NC][256 / K],
                                        int32_t *s_col = nullptr) {
@@ -670,21 +799,6 @@ __device__ inline void efs_forces_body(const EfsArgs &a, int64_t blk, T *c_s, T 
         }
         gstart += tc;
     }
-    if constexpr (R > 0 && LV::STAGED) {   // (the single-kernel contraction writes these for the other levels)
-        if (brow) {   // species one-hot, zero c blocks of the other central species, zero padding
-            for (int k = sub; k < nt; k += K) brow[k * ldn] = k == c.zi ? 1.0 : 0.0;
-            if constexpr (R == 2) {
-                const int nblk = NR * nt * nt * NPOLY;
-                for (int k = sub; k < nblk; k += K) {
-                    const int zz = (k / (nt * NPOLY)) % nt;
-                    if (zz == c.zi) continue;
-                    const int col = s_col[k];
-                    if (col >= 0) brow[col * ldn] = 0.0;
-                }
-            }
-            for (int k = a.m + sub; k < a.ldb; k += K) brow[k * ldn] = 0.0;
-        }
-    }
     if constexpr (G) {
 #pragma unroll
         for (int o = K / 2; o > 0; o >>= 1)
@@ -711,9 +825,8 @@ __device__ inline void efs_forces_body(const EfsArgs &a, int64_t blk, T *c_s, T 
 // ---- kernel 4: the rest of b_i (Sec. II.C); LANES per atom ----------------
 // FULL grade mode: the radial-coefficient part
 //   dV_i/dc_{mu, z_i, z_j, beta} = sum_{j of species z_j} T_beta(r_ij) (R_cut - r_ij)^2 P_mu(r_ij)
-// (P_mu as in kernel 3), zero for the blocks of the other central species;
-// both modes: the species one-hot (dV_i/dxi0) and zero padding.  The
-// xi part (B_alpha) comes from kernel 2.
+// (P_mu as in kernel 3).  The rest (B_alpha, one-hot, zeros) comes from
+// kernel 2.
 template <typename T, int L, int K>
 __device__ inline void efs_rows_body(const EfsArgs &a, int64_t blk, T (&s_dm)[Level<L>::NC][256 / K],
                                      int32_t *s_col) {
@@ -793,24 +906,6 @@ __device__ inline void efs_rows_body(const EfsArgs &a, int64_t blk, T (&s_dm)[Le
             gstart += tc;
         }
     }
-    if (brow) {
-        // species one-hot, zero c blocks of the other central species, zero
-        // padding: written here for the staged levels only (the single-kernel
-        // contraction writes them for the others)
-        if constexpr (Level<L>::STAGED) {
-            for (int k = sub; k < nt; k += K) brow[k * ldn] = k == c.zi ? 1.0 : 0.0;
-            if (full_rows) {
-                const int nblk = NR * nt * nt * NPOLY;
-                for (int k = sub; k < nblk; k += K) {
-                    const int zz = (k / (nt * NPOLY)) % nt;
-                    if (zz == c.zi) continue;
-                    const int col = s_col[k];
-                    if (col >= 0) brow[col * ldn] = 0.0;
-                }
-            }
-            for (int k = a.m + sub; k < a.ldb; k += K) brow[k * ldn] = 0.0;
-        }
-    }
 }
 
 // Kernels 3 and 4 in one launch: blocks [0, nblk) take kernel 3, blocks
@@ -885,11 +980,11 @@ template <int L, typename TF, typename TD> int launch_fr_level_t(const EfsArgs &
     template <typename T, int K, bool WB> static void launch_mc##LEVEL(const EfsArgs &a) {               \
         const unsigned grid = (unsigned)((a.n_atoms + 256 / K - 1) / (256 / K));                         \
         const unsigned grid1 = (unsigned)((a.n_atoms + 63) / 64);                                        \
-        if (K == 4) {                                                                                    \
+        if constexpr (K == 4 && contract_waves<LEVEL>() == 4) {                                          \
             ProfScope ps("efs_moments", a.stream);                                                       \
             hipLaunchKernelGGL((efs_moments_contract<T, LEVEL, WB>), dim3(grid1), dim3(256), 0, a.stream, \
                                a);                                                                       \
-        } else if (K == 8) {                                                                             \
+        } else if constexpr (K == 8) {                                                                           \
             ProfScope ps("efs_moments", a.stream);                                                       \
             hipLaunchKernelGGL((efs_moments_contract8<T, LEVEL, WB>), dim3(grid1), dim3(512), 0,          \
                                a.stream, a);                                                             \
@@ -899,7 +994,8 @@ template <int L, typename TF, typename TD> int launch_fr_level_t(const EfsArgs &
                 hipLaunchKernelGGL((efs_moments<T, LEVEL, K>), dim3(grid), dim3(256), 0, a.stream, a);   \
             }                                                                                            \
             ProfScope ps("efs_contract", a.stream);                                                      \
-            hipLaunchKernelGGL((efs_contract<T, LEVEL, WB>), dim3(grid1), dim3(256), 0, a.stream, a);    \
+            hipLaunchKernelGGL((efs_contract<T, LEVEL, WB>), dim3(grid1),                                \
+                               dim3(64 * contract_waves<LEVEL>()), 0, a.stream, a);                      \
         }                                                                                                \
     }                                                                                                    \
     template <> int launch_mc_level_t<LEVEL, TT>(const EfsArgs &a) {                                     \

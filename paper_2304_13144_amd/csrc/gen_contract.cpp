@@ -1,5 +1,7 @@
 // Build-time generator: writes one HIP header per MTP level with the
-// straight-line contraction program of that level.
+// straight-line contraction program of that level, in the factorised form
+// (contract_dag.hpp) and, up to level 16, in the expanded form that the FP32
+// contraction runs.
 //
 // For a neighborhood with moment components M (see basis.hpp) the program
 // computes
@@ -25,6 +27,7 @@
 #include <vector>
 
 #include "basis.hpp"
+#include "contract_dag.hpp"
 
 using namespace mtp;
 
@@ -381,10 +384,9 @@ struct Emitter {
     }
 };
 
-// Levels with more connected graphs than this get the staged program: graph
-// values, trie walk and reverse pass as separate kernels (graph values and
-// dV/dg pass through memory), each split into parts that compile apart.
-constexpr int STAGED_GRAPHS = 128;
+// The staged form (--staged; the library does not use it: it checks the other
+// forms on the host): graph values, trie walk and reverse pass apart, each
+// split into parts.
 constexpr int STAGE_G = 8, STAGE_R = 16;
 
 // Split for the staged program: graphs (largest first) go to the part whose
@@ -543,13 +545,89 @@ void write_level_staged(const std::string &dir, int level, const Basis &B) {
               << cr.flops() << " (staged: " << STAGE_G << " graph parts, " << STAGE_R << " reverse parts)\n";
 }
 
+// Levels above this have the factorised program only; up to it the expanded
+// program is written too: the FP32 contraction runs it (its results keep the
+// rounding they have), FP64 and the training backward run the factorised one
+// at every level.
+constexpr int EXPANDED_MAX = 16;
+
+// The factorised program (contract_dag.hpp) in clusters for kernels of four
+// and of eight wavefronts; wavefront NW - 1 also takes the low graphs.
+void write_factorised(std::ostringstream &h, const Basis &B, long &flops) {
+    dag::Factorised F(B);
+    const dag::Cluster lc = F.make_cluster(F.low);
+    auto list = [&](const std::vector<int> &v) {
+        std::string o;
+        for (int x : v) o += (o.empty() ? "" : ",") + std::to_string(x);
+        return v.empty() ? std::string("-1") : o;
+    };
+    long fl = 0;
+    const std::string lv = F.low.empty() ? "" : F.emit_low_values(lc, fl);
+    const std::string lf = F.emit_low_functions(fl), lcp = F.emit_coupling(fl),
+                      lr = F.emit_low_reverse(lc, fl);
+    const int nl = (int)F.low.size(), np = F.n_prods();
+    h << "\n  // factorised program: NLOW graphs up to half the level, NPROD products of them that occur beside a\n"
+         "  // graph above it; fcomp*: the sums a cluster adds to (component k of dV/dM: k, X_p: NC + p)\n";
+    h << "  static constexpr int NLOW = " << nl << ", NPROD = " << np << ";\n";
+    h << "  static constexpr int NLOWC = " << lc.comps.size() << ";\n";
+    h << "  static constexpr int low_comp[" << std::max<size_t>(1, lc.comps.size()) << "] = {" << list(lc.comps) << "};\n";
+    for (int nw : {4, 8}) {
+        // the last wavefront's share shrinks by the low functions' walk
+        std::vector<dag::Cluster> cl = F.clusters(F.high, nw, 8, 3 * (long)F.n_low_functions());
+        size_t mx = 1;
+        const int NC = B.n_comp();
+        for (auto &c : cl) mx = std::max(mx, c.rows(NC).size());
+        h << "  static constexpr int FMAX" << nw << " = " << mx << ";\n";
+        h << "  static constexpr int fncomp" << nw << "[" << nw << "] = {";
+        for (int q = 0; q < nw; ++q) h << (q ? "," : "") << cl[q].rows(NC).size();
+        h << "};\n  static constexpr int fcomp" << nw << "[" << nw << "][" << mx << "] = {";
+        for (int q = 0; q < nw; ++q) h << (q ? ", " : "") << "{" << (cl[q].comps.empty() ? "0" : list(cl[q].rows(NC))) << "}";
+        h << "};\n";
+        h << "  template <int P, bool WB, typename T, typename MP, typename XP, typename BP>\n";
+        h << "  __device__ __forceinline__ static void fact" << nw << "(MP M, const T *p, XP xi, BP Bout, T *d) {\n";
+        long cf = 0;
+        for (int q = 0; q < nw; ++q)
+            h << "  " << (q ? "else " : "") << "if constexpr (P == " << q << ") {\n" << F.emit_cluster(cl[q], cf) << "  }\n";
+        h << "  }\n";
+        if (nw == 4) flops = fl + cf;
+    }
+    h << "  template <typename T, typename MP>\n";
+    h << "  __device__ __forceinline__ static void low_values(MP M, T *gl, T *p) {\n" << lv << "  }\n";
+    h << "  template <bool WB, typename T, typename XP, typename BP>\n";
+    h << "  __device__ __forceinline__ static void low_functions(const T *gl, XP xi, BP Bout, T *dz, T &V) {\n" << lf
+      << "  }\n";
+    h << "  template <typename T>\n";
+    h << "  __device__ __forceinline__ static void low_coupling(const T *gl, const T *p, const T *X, T *dz, T &V) {\n"
+      << lcp << "  }\n";
+    h << "  template <typename T, typename MP>\n";
+    h << "  __device__ __forceinline__ static void low_reverse(MP M, const T *dz, T *d) {\n" << lr << "  }\n";
+}
+
 bool force_staged = false;   // --staged: every level as a staged program (for checking the two forms)
-bool force_single = false;   // --single: every level as one program
+bool force_single = false;   // --single: every level as one expanded program
+bool force_factorised = false;   // --factorised: every level as the factorised program alone
 
 void write_level(const std::string &dir, int level) {
     Basis B = build_basis(level);
-    if (force_staged || (!force_single && (int)B.graphs.size() > STAGED_GRAPHS))
-        return write_level_staged(dir, level, B);
+    if (force_staged) return write_level_staged(dir, level, B);
+    if (force_factorised || (!force_single && level > EXPANDED_MAX)) {
+        std::ostringstream h;
+        long flops = 0;
+        h << "// generated by gen_contract for MTP level " << level << "; do not edit.\n";
+        h << "// " << B.graphs.size() << " connected graphs, " << B.n_lin() << " basis functions, " << B.n_comp()
+          << " moment components, " << B.n_rad << " radial functions.\n";
+        h << "#pragma once\n\ntemplate <> struct Level<" << level << "> {\n";
+        write_common(h, B, level);
+        h << "  static constexpr bool EXPANDED = false;\n";
+        write_factorised(h, B, flops);
+        h << "  // flops of the contraction program per neighborhood (mul/add = 1, fma = 2)\n";
+        h << "  static constexpr long FLOPS = " << flops << ";\n};\n";
+        std::ofstream out(dir + "/mtp_level" + std::to_string(level) + ".inc");
+        out << h.str();
+        std::cout << "level " << level << ": graphs " << B.graphs.size() << " basis " << B.n_lin() << " comps "
+                  << B.n_comp() << " flops " << flops << " (factorised)\n";
+        return;
+    }
     Emitter em(B);
     std::vector<int> all(B.graphs.size());
     for (size_t G = 0; G < all.size(); ++G) all[G] = (int)G;
@@ -628,7 +706,7 @@ void write_level(const std::string &dir, int level) {
     h << "  static constexpr long FLOPS_GRAPHS = " << cf.flops() << ";\n";
     h << "  static constexpr long FLOPS_TRIE = " << ct.flops() << ";\n";
     h << "  static constexpr long FLOPS_REVERSE = " << cr.flops() << ";\n";
-    h << "  static constexpr bool STAGED = false;\n";
+    h << "  static constexpr bool EXPANDED = true;\n";
     h << "  static constexpr int NPART = " << NPART << ";\n";
     h << "  static constexpr int graph_part[" << B.graphs.size() << "] = {";
     for (size_t G = 0; G < B.graphs.size(); ++G) h << (G ? "," : "") << s4.part[G];
@@ -678,6 +756,11 @@ void write_level(const std::string &dir, int level) {
     h << walk_arrays << "  }\n";
     parts("reverse_part", "(MP M, const T *dgin, T (&dM)[NC])", s4.pr);
     parts("reverse_part8", "(MP M, const T *dgin, T (&dM)[NC])", s8.pr);
+    if (!force_single) {
+        long flops = 0;
+        write_factorised(h, B, flops);
+        h << "  static constexpr long FLOPS = " << flops << ";   // of the factorised program, per neighborhood\n";
+    }
     h << "};\n";
     std::ofstream out(dir + "/mtp_level" + std::to_string(level) + ".inc");
     out << h.str();
@@ -693,8 +776,9 @@ int main(int argc, char **argv) {
         return 2;
     }
     for (int i = 2; i < argc; ++i) {
-        if (std::string(argv[i]) == "--staged" || std::string(argv[i]) == "--single") {
-            (argv[i][2] == 's' && argv[i][3] == 't' ? force_staged : force_single) = true;
+        const std::string arg = argv[i];
+        if (arg == "--staged" || arg == "--single" || arg == "--factorised") {
+            (arg == "--staged" ? force_staged : arg == "--single" ? force_single : force_factorised) = true;
             continue;
         }
         write_level(argv[1], std::atoi(argv[i]));

@@ -82,9 +82,8 @@ struct mtp_model {
     int force_grade = 0;            // set while the tuner times a grade schedule
     int tuned_grade[2][2][48] = {}; // [precision][grade mode][floor(log2 n_atoms)] -> GRADE_*, 0 = untuned
     // scratch of the evaluation path
-    mutable mtp::DevBuf gbuf, virial, sitebuf, brow, gamma_ws, argmax_ws, work, sums, mbuf, dmbuf, tbuf, dtbuf, rows;
+    mutable mtp::DevBuf gbuf, virial, sitebuf, brow, gamma_ws, argmax_ws, work, sums, mbuf, dmbuf, dtbuf, rows;
     mutable mtp::DevBuf selblk;     // per-block preselection counts written by the grade kernels
-    mutable mtp::DevBuf gval, dgval;   // staged levels: graph values and dV/dg between the launches
     mutable mtp::DevBuf cfgrows, cfgpart;   // configuration-mode rows and their chunk partials
     mutable mtp::DevBuf md_f, md_g, md_invm, md_scal;   // MD driver: forces, grades, 1/mass, {gamma max, norms}
     mutable mtp::DevBuf md_v;                           // relaxation: FIRE velocities
@@ -120,11 +119,11 @@ namespace mtp {
 int launch_efs(int level, const EfsArgs &a);
 
 int launch_backward(int level, const BwdArgs &b);
-void launch_column_sums(const void *rows, int precision, int64_t n, int ncol, double *out, hipStream_t st,
-                        DevBuf &work);
+bool has_backward(int level);        // levels whose training backward is compiled
+void launch_theta_sums(const void *cols, int precision, int64_t ldn, int64_t n, int n_lin, int n_rad, int nt, const int32_t *type,
+                       const double *gE, const int32_t *atom_cfg, double *out, hipStream_t st, DevBuf &work);
 std::vector<int> compiled_levels();
 long contraction_flops(int level);   // per neighborhood, from the generated program
-int staged_graphs(int level);        // connected graphs of a level compiled as a staged program, else 0
 
 void build_neighbors(const mtp_model *m, const mtp_system *s, int max_nbrs, mtp_nbrs *nb, hipStream_t st);
 
@@ -221,9 +220,9 @@ int64_t launch_fit_residual(int64_t n, const double *y, const double *t, double 
                             hipStream_t st);
 // configuration-mode rows: out (column-major, entry (c, k) at out[k * n_cfg + c])
 // = per-configuration sums of the column-major FP64 rows (entry (i, k) at
-// rows[k * n + i], ldb columns); part: cfg_row_partials_bytes(n, ldb)
+// rows[k * ldn + i], ldb columns); part: cfg_row_partials_bytes(n, ldb)
 size_t cfg_row_partials_bytes(int64_t n, int ldb);
-void launch_cfg_rows(const double *rows, int ldb, int64_t n, const mtp_system *s, double *part, double *out,
+void launch_cfg_rows(const double *rows, int64_t ldn, int ldb, int64_t n, const mtp_system *s, double *part, double *out,
                      hipStream_t st);
 void launch_zero(void *p, size_t bytes, hipStream_t st);
 

@@ -33,7 +33,7 @@ struct EfsArgs {
     double *F;                // [N*3] with gbuf: sum_j dV_i/dr_ij per atom (the gather subtracts the rest)
     double *virial;           // [n_atoms*9]
     double *brow;             // rows b_i, FP64, column-major: entry (i, k) at brow[k * ldn + i]
-    int64_t ldn;              // column stride of brow (>= n_atoms)
+    int64_t ldn;              // column stride of brow: n_atoms rounded up to whole blocks of 64
     int ldb;                  // columns written: m, then zeros up to ldb
     int grade_mode;           // rows layout: FULL (with colmap) or LINEAR
     const int32_t *colmap;    // full column -> kept column or -1
@@ -42,7 +42,6 @@ struct EfsArgs {
     int lanes;                // lanes per neighborhood of the pair-gradient / row kernel (2, 4, 8)
     int lanes_mc;             // lanes per neighborhood of the moments / contraction (2, 4, 8; 4 = one launch)
     void *mbuf, *dmbuf;       // [NC][n_atoms] T: moments and dV/dM between the kernels
-    void *gval, *dgval;       // staged levels only: [NGRAPH][n_atoms] T graph values and dV/dg
     // optional (atom_list NULL only): the pair-gradient blocks also write the
     // per-32-atom partial sums of part_e (V_i, nullable) and virial into part
     double *part;
@@ -50,13 +49,12 @@ struct EfsArgs {
     hipStream_t stream;
 };
 struct BwdArgs {
-    EfsArgs e;                // neighbors, parameters, mbuf (moments), dmbuf (dV/dM)
+    EfsArgs e;                // neighbors, parameters, dmbuf (dV/dM)
     const double *gE, *gF, *gS;
     const int32_t *atom_cfg;
     const int32_t *nbr_j;
-    void *tbuf, *dtbuf;       // [NC][n] tangent moments and H Mdot
-    void *rows;               // [n][n_theta] T: per-neighborhood gradient contributions
-    int n_theta;
+    void *dtbuf;              // [NC][n] H Mdot
+    void *cols;               // [n_lin + n_types N_rad NPOLY][e.ldn] T: per-neighborhood gradient contributions
 };
 // Optional timing of library kernels with HIP events (see mtp_profile_enable).
 void prof_mark(const char *name, bool begin, hipStream_t st);

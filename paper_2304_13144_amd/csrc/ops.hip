@@ -149,26 +149,26 @@ __global__ __launch_bounds__(256) void cfg_final(const int64_t *cfg_off, const d
 // ... of its chunk's rows in atom order), then one block per configuration
 // adds the partials of its whole chunks and the rows of the chunks it shares
 // with its neighbors.  Fixed order throughout.  Rows and results are
-// column-major (entry (i, k) at rows[k * n + i]).
+// column-major (entry (i, k) at rows[k * ldn + i]).
 constexpr int ROW_CHUNK = 64;
-__global__ __launch_bounds__(256) void row_partials(const double *rows, int ldb, int64_t n, double *part) {
+__global__ __launch_bounds__(256) void row_partials(const double *rows, int64_t ldn, int ldb, int64_t n, double *part) {
     const int64_t a0 = (int64_t)blockIdx.x * ROW_CHUNK;
     const int64_t a1 = a0 + ROW_CHUNK < n ? a0 + ROW_CHUNK : n;
     for (int k = threadIdx.x; k < ldb; k += 256) {
-        const double *col = rows + (int64_t)k * n;
+        const double *col = rows + (int64_t)k * ldn;
         double acc = 0.0;
         for (int64_t i = a0; i < a1; ++i) acc += col[i];
         part[(int64_t)blockIdx.x * ldb + k] = acc;
     }
 }
 
-__global__ __launch_bounds__(256) void row_final(const double *rows, int ldb, int64_t n, const double *part,
+__global__ __launch_bounds__(256) void row_final(const double *rows, int64_t ldn, int ldb, int64_t n, const double *part,
                                                  const int64_t *cfg_off, int n_cfg, double *out) {
     const int c = blockIdx.x;
     const int64_t b = cfg_off[c], e = cfg_off[c + 1];
     const int64_t cb = (b + ROW_CHUNK - 1) / ROW_CHUNK, ce = e / ROW_CHUNK;   // whole chunks [cb, ce)
     for (int k = threadIdx.x; k < ldb; k += 256) {
-        const double *col = rows + (int64_t)k * n;
+        const double *col = rows + (int64_t)k * ldn;
         double acc = 0.0;
         if (cb < ce) {
             for (int64_t i = b; i < cb * ROW_CHUNK; ++i) acc += col[i];
@@ -453,46 +453,83 @@ __global__ __launch_bounds__(256) void select_write(const double *g, int64_t n, 
     if (gb < nb) select_write_wave<SCANNED>(gb, nb, g, n, thr, blk, per, idx, cap, count);
 }
 
-// column sums of the per-neighborhood gradient rows, FP64, fixed order:
-// block (column tile, atom chunk) -> partial; then partials in chunk order
-constexpr int CS_CH = 64;
+// dL/dtheta from the per-neighborhood contributions (column-major, see
+// backward_kernel.hpp), FP64, fixed order: block (column, chunk of CS_CHUNK
+// neighborhoods) adds one column's entries -- consecutive threads read
+// consecutive neighborhoods -- by central species where the column stands for
+// one entry per species, and writes the theta entries it stands for (into
+// its chunk's partial theta, or straight into the result when one chunk
+// holds all neighborhoods).  The last column is xi_0: the sum of dL/dE over
+// the neighborhoods of each species.
+constexpr int CS_CHUNK = 4096;
 template <typename T>
-__global__ __launch_bounds__(256) void col_partial(const T *rows, int64_t n, int ncol, double *part) {
-    const int col = blockIdx.x * 64 + (threadIdx.x & 63), g = threadIdx.x >> 6;
-    const int64_t chunk = (n + CS_CH - 1) / CS_CH;
-    const int64_t i0 = (int64_t)blockIdx.y * chunk, i1 = i0 + chunk < n ? i0 + chunk : n;
-    double s = 0.0;
-    if (col < ncol)
-        for (int64_t i = i0 + g; i < i1; i += 4) s += double(rows[i * ncol + col]);
-    __shared__ double sh[4][64];
-    sh[g][threadIdx.x & 63] = s;
+__global__ __launch_bounds__(256) void theta_sums(const T *cols, int64_t ldn, int64_t n, int n_lin, int n_rad, int nt,
+                                                  const int32_t *type, const double *gE, const int32_t *atom_cfg,
+                                                  double *out, int n_theta) {
+    __shared__ double sh[4][MAX_TYPES];
+    const int col = blockIdx.x, nc = nt * n_rad * NPOLY;
+    const int64_t i0 = (int64_t)blockIdx.y * CS_CHUNK, i1 = i0 + CS_CHUNK < n ? i0 + CS_CHUNK : n;
+    const bool by_type = col >= n_lin, xi0 = col == n_lin + nc;
+    double acc[MAX_TYPES];
+#pragma unroll
+    for (int z = 0; z < MAX_TYPES; ++z) acc[z] = 0.0;
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += 256) {
+        const double v = xi0 ? (gE ? gE[atom_cfg[i]] : 0.0) : double(cols[(int64_t)col * ldn + i]);
+        int zi = by_type ? type[i] : 0;
+        zi = zi < 0 ? 0 : (zi >= nt ? nt - 1 : zi);
+#pragma unroll
+        for (int z = 0; z < MAX_TYPES; ++z) acc[z] += z == zi ? v : 0.0;
+    }
+#pragma unroll
+    for (int z = 0; z < MAX_TYPES; ++z)
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) acc[z] += __shfl_xor(acc[z], o, 64);
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int z = 0; z < MAX_TYPES; ++z) sh[threadIdx.x >> 6][z] = acc[z];
     __syncthreads();
-    if (g == 0 && col < ncol)
-        part[(int64_t)blockIdx.y * ncol + col] = ((sh[0][threadIdx.x] + sh[1][threadIdx.x]) + sh[2][threadIdx.x]) +
-                                                 sh[3][threadIdx.x];
+    if ((int)threadIdx.x < (by_type ? nt : 1)) {
+        const int z = threadIdx.x;
+        int k = nt + col;
+        if (xi0) {
+            k = z;
+        } else if (by_type) {   // column (t, mu, beta) of species z: c[mu][z][t][beta]
+            const int q = col - n_lin, t = q / (n_rad * NPOLY), mu = (q / NPOLY) % n_rad;
+            k = nt + n_lin + ((mu * nt + z) * nt + t) * NPOLY + q % NPOLY;
+        }
+        out[(int64_t)blockIdx.y * n_theta + k] = ((sh[0][z] + sh[1][z]) + sh[2][z]) + sh[3][z];
+    }
 }
 
-__global__ void col_final(const double *part, int ncol, double *out) {
-    const int col = blockIdx.x * blockDim.x + threadIdx.x;
-    if (col >= ncol) return;
+__global__ void theta_final(const double *part, int n_theta, int chunks, double *out) {
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n_theta) return;
     double s = 0.0;
-    for (int ch = 0; ch < CS_CH; ++ch) s += part[(int64_t)ch * ncol + col];
-    out[col] = s;
+    for (int ch = 0; ch < chunks; ++ch) s += part[(int64_t)ch * n_theta + k];
+    out[k] = s;
 }
 
 }  // namespace
 
-void launch_column_sums(const void *rows, int precision, int64_t n, int ncol, double *out, hipStream_t st,
-                        DevBuf &work) {
-    work.ensure(sizeof(double) * CS_CH * (size_t)ncol);
-    const dim3 grid((unsigned)((ncol + 63) / 64), CS_CH);
+void launch_theta_sums(const void *cols, int precision, int64_t ldn, int64_t n, int n_lin, int n_rad, int nt, const int32_t *type,
+                       const double *gE, const int32_t *atom_cfg, double *out, hipStream_t st, DevBuf &work) {
+    const int n_theta = nt + n_lin + n_rad * nt * nt * NPOLY, ncol = n_lin + nt * n_rad * NPOLY + 1;
+    const int chunks = (int)((n + CS_CHUNK - 1) / CS_CHUNK);
+    double *dst = out;
+    if (chunks > 1) {
+        work.ensure(sizeof(double) * (size_t)chunks * n_theta);
+        dst = work.as<double>();
+    }
+    const dim3 grid((unsigned)ncol, (unsigned)chunks);
     if (precision == MTP_FP64)
-        hipLaunchKernelGGL(col_partial<double>, grid, dim3(256), 0, st, static_cast<const double *>(rows), n, ncol,
-                           work.as<double>());
+        hipLaunchKernelGGL(theta_sums<double>, grid, dim3(256), 0, st, static_cast<const double *>(cols), ldn, n, n_lin,
+                           n_rad, nt, type, gE, atom_cfg, dst, n_theta);
     else
-        hipLaunchKernelGGL(col_partial<float>, grid, dim3(256), 0, st, static_cast<const float *>(rows), n, ncol,
-                           work.as<double>());
-    hipLaunchKernelGGL(col_final, dim3((unsigned)((ncol + 255) / 256)), dim3(256), 0, st, work.as<double>(), ncol, out);
+        hipLaunchKernelGGL(theta_sums<float>, grid, dim3(256), 0, st, static_cast<const float *>(cols), ldn, n, n_lin,
+                           n_rad, nt, type, gE, atom_cfg, dst, n_theta);
+    if (chunks > 1)
+        hipLaunchKernelGGL(theta_final, dim3((unsigned)((n_theta + 255) / 256)), dim3(256), 0, st, dst, n_theta, chunks,
+                           out);
 }
 
 // Scratch of mtp_energy_forces_stress_noalloc: a file-scope device array
@@ -562,12 +599,12 @@ size_t cfg_row_partials_bytes(int64_t n, int ldb) {
     return sizeof(double) * (size_t)ldb * (size_t)std::max<int64_t>(1, (n + ROW_CHUNK - 1) / ROW_CHUNK);
 }
 
-void launch_cfg_rows(const double *rows, int ldb, int64_t n, const mtp_system *s, double *part, double *out,
+void launch_cfg_rows(const double *rows, int64_t ldn, int ldb, int64_t n, const mtp_system *s, double *part, double *out,
                      hipStream_t st) {
     if (s->n_cfg <= 0) return;
     const unsigned nch = (unsigned)((n + ROW_CHUNK - 1) / ROW_CHUNK);
-    if (nch) hipLaunchKernelGGL(row_partials, dim3(nch), dim3(256), 0, st, rows, ldb, n, part);
-    hipLaunchKernelGGL(row_final, dim3((unsigned)s->n_cfg), dim3(256), 0, st, rows, ldb, n, part, s->cfg_off,
+    if (nch) hipLaunchKernelGGL(row_partials, dim3(nch), dim3(256), 0, st, rows, ldn, ldb, n, part);
+    hipLaunchKernelGGL(row_final, dim3((unsigned)s->n_cfg), dim3(256), 0, st, rows, ldn, ldb, n, part, s->cfg_off,
                        s->n_cfg, out);
 }
 
