@@ -30,6 +30,8 @@
 // the MaxVol swap loop with Sherman-Morrison updates (FP64 only).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace mtp {
@@ -751,14 +753,17 @@ __global__ __launch_bounds__(512) void grade_i8(const double *__restrict__ brow,
     }
 }
 
-// D_k = 2^-round(log2 max_i |A_ik|) (0 past m, and for an all-zero column)
-__global__ void i8_colscale(const double *A, int m, int KP, double *dsc) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= KP) return;
+// D_k = 2^-round(log2 max_i |A_ik|) (0 past m, and for an all-zero column).
+// One wavefront per column: the column's loads are in flight together (one
+// thread per column waited for m loads in a row: 51 us at m = 212, now 4 us).
+__global__ __launch_bounds__(64) void i8_colscale(const double *A, int m, double *dsc) {
+    const int k = blockIdx.x;
     double mx = 0.0;
     if (k < m)
-        for (int i = 0; i < m; ++i) mx = fmax(mx, fabs(A[(int64_t)i * m + k]));
-    dsc[k] = mx > 0.0 ? ldexp(1.0, -(int)rint(log2(mx))) : 0.0;
+        for (int i = threadIdx.x; i < m; i += 64) mx = fmax(mx, fabs(A[(int64_t)i * m + k]));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+    if (threadIdx.x == 0) dsc[k] = mx > 0.0 ? ldexp(1.0, -(int)rint(log2(mx))) : 0.0;
 }
 
 // digits of column c of D^-1 A^-1, stored in the order the grade's lanes read
@@ -795,216 +800,595 @@ __global__ __launch_bounds__(256) void i8_slice_ainv(const double *Ainv, int m, 
     }
 }
 
-// ---- Gauss-Jordan inverse ---------------------------------------------------
-// W = [A | I] (m x 2m, row-major) becomes [I | A^-1] by m elimination steps
-// with partial pivoting (largest |W[r][c]| over r >= c, the lowest row on
-// ties).  One launch per step c, one block per row r: every block finds the
-// pivot p itself (the same search over column c in every block, so no
-// grid-wide exchange is needed) and writes row r of the next W from the
-// current one (two buffers: no block reads what another writes):
-//   next[c] = cur[p] / cur[p][c]
-//   next[p] = cur[c] - cur[c][c] next[c]          (p != c)
-//   next[r] = cur[r] - cur[r][c] next[c]          (other rows)
-// with column c set to the unit vector e_c exactly.  A pivot below 1e-300
-// sets *singular, and every later step returns at once.
-constexpr int GJ_T = 256;
-__global__ __launch_bounds__(GJ_T) void gj_step(const double *__restrict__ cur, double *__restrict__ next, int m,
-                                                int c, int32_t *singular) {
-    __shared__ double sv[GJ_T / 64];
-    __shared__ int si[GJ_T / 64];
-    if (*singular) return;   // uniform: the flag was written by an earlier launch
-    const int n2 = 2 * m, r = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    double bv = -1.0;
-    int bi = m;
-    for (int q = c + tid; q < m; q += GJ_T) {
-        const double v = fabs(cur[(int64_t)q * n2 + c]);
-        if (v > bv) {   // rows visited in increasing order: the first maximum is kept
-            bv = v;
-            bi = q;
+// ---- reductions over a wavefront ----------------------------------------------
+// largest x of the wavefront, in every lane (DPP: lanes without a source keep their own)
+template <int CTRL> __device__ inline uint32_t dpp_max(uint32_t x) {
+    const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, 0xf, 0xf, false);
+    return x > y ? x : y;
+}
+__device__ inline uint32_t wave_max_u32(uint32_t x) {
+    x = dpp_max<0x111>(x);   // row_shr:1
+    x = dpp_max<0x112>(x);   // row_shr:2
+    x = dpp_max<0x114>(x);   // row_shr:4
+    x = dpp_max<0x118>(x);   // row_shr:8
+    x = dpp_max<0x142>(x);   // row_bcast:15
+    x = dpp_max<0x143>(x);   // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+__device__ inline double lane_value(double x, int lane) {   // lane: uniform
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+// Largest of the lanes' keys (the bits of non-negative doubles; 0: none), the
+// lowest tag among equal ones: the high words by DPP, then the few lanes that
+// hold it (usually one)
+__device__ inline void wave_first(unsigned long long key, int tag, unsigned long long &bk, int &bt) {
+    const uint32_t hi = wave_max_u32((uint32_t)(key >> 32));
+    unsigned long long have = __ballot((uint32_t)(key >> 32) == hi);
+    bk = 0;
+    bt = 0x7fffffff;
+    if (hi == 0) {   // uniform: all keys tiny or none
+        have = __ballot(key != 0);
+    }
+    while (have) {
+        const int l = __ffsll(have) - 1;
+        const unsigned long long k = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(key >> 32), l) << 32 |
+                                     (uint32_t)__builtin_amdgcn_readlane((int)key, l);
+        const int t = __builtin_amdgcn_readlane(tag, l);
+        if (k > bk || (k == bk && t < bt)) {
+            bk = k;
+            bt = t;
         }
+        have &= have - 1;
+    }
+}
+
+// ---- Gauss-Jordan inverse ---------------------------------------------------
+// W = A becomes A^-1 in place by m elimination steps with partial pivoting
+// (largest |W[r][c]| over the rows not used yet, the lowest row on ties),
+// GJ_P steps per pair of launches.  Rows stay where they are.  Step c with
+// pivot row p, f_r = W[r][c] and u = W[p] / W[p][c] (u_c = 1 / W[p][c]):
+//   W[p] = u;   W[r] = W[r] - f_r u  (other rows, with W[r][c] counted as 0)
+// so that column c takes the column of the identity half which the step
+// brings to life.  gj_panel (one block, a thread per row) runs the steps on
+// the panel's own columns, where the pivots come from: each wavefront offers
+// its largest open row, one barrier, the best of the offers is the pivot row.
+// It leaves f of every step.  gj_apply (a block per 16 other columns) takes the
+// pivot rows through the steps, then every entry, each from registers.  A
+// pivot below 1e-300 sets *singular, and every later launch returns at once.
+// Bound by the panel's serial chain (about 1.4 us a step: search, barrier,
+// pivot row, update, one wavefront per SIMD) and the launches; one launch per
+// step that read and wrote [W | I] took 917 us at m = 212, the 28 launches
+// here 540 us.  (One block holding all of W in registers measured 485-650 us
+// and spilled at m > 192.)
+constexpr int GJ_P = 16, GJ_T = 1024;   // columns per panel; threads of a panel block at most
+
+struct GJBuf {
+    double *W;             // [m][m]
+    double *F;             // [m][GJ_P] f of the panel's steps per row
+    double *inv;           // [GJ_P] 1 / pivot
+    int32_t *piv;          // [GJ_P] pivot row of the panel's steps
+    int32_t *step;         // [m] step a row is pivot of, -1: open
+    int32_t *at;           // [m] pivot row of a step
+    int32_t *singular;
+};
+
+__global__ void gj_setup(const double *A, int m, GJBuf B) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e < (int64_t)m * m) B.W[e] = A[e];
+    if (e < m) B.step[e] = -1;
+    if (e == 0) *B.singular = 0;
+}
+
+template <int RP, int NT>   // rows per thread, threads at most (fewer leave each more registers: 16 + 16 doubles a row)
+__global__ __launch_bounds__(NT) void gj_panel(int m, int c0, GJBuf B) {
+    __shared__ double cand[2][NT / 64][GJ_P + 1];   // each wavefront's candidate row of a step and 1 / its pivot
+    __shared__ unsigned long long ckey[2][NT / 64];
+    __shared__ int crow[2][NT / 64];
+    if (*B.singular) return;   // uniform: the flag was written by an earlier launch
+    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6, waves = nt >> 6;
+    const int nq = m - c0 < GJ_P ? m - c0 : GJ_P;
+    bool bad = false;
+    double T[RP][GJ_P], f[RP][GJ_P], my_inv[RP];
+    int step[RP];
+#pragma unroll
+    for (int s = 0; s < RP; ++s) {
+        const int r = tid + nt * s;
+        my_inv[s] = 0.0;
+        step[s] = r < m ? B.step[r] : 0;
+#pragma unroll
+        for (int k = 0; k < GJ_P; ++k) T[s][k] = r < m && k < nq ? B.W[(int64_t)r * m + c0 + k] : 0.0;
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const double ov = __shfl_xor(bv, o, 64);
-        const int oi = __shfl_xor(bi, o, 64);
-        if (ov > bv || (ov == bv && oi < bi)) {
-            bv = ov;
-            bi = oi;
+    for (int q = 0; q < GJ_P; ++q) {
+        if (q >= nq) {   // uniform: past the last column a step does nothing
+#pragma unroll
+            for (int s = 0; s < RP; ++s) f[s][q] = 0.0;
+            continue;
+        }
+        constexpr int two = 2;
+        const int buf = q % two;   // read after this step's barrier, written again after the next one's
+        unsigned long long key = 0;   // the bits of the largest |W|, 0: none (NaN included)
+        double own = 1.0;
+        int row = 0;
+#pragma unroll
+        for (int s = 0; s < RP; ++s) {
+            const double v = fabs(T[s][q]);
+            const unsigned long long kv = step[s] < 0 && v == v ? (unsigned long long)__double_as_longlong(v) : 0ull;
+            if (kv > key) {
+                key = kv;
+                own = T[s][q];
+                row = tid + nt * s;
+            }
+        }
+        const double own_inv = 1.0 / own;   // every lane's own, beside the search
+        unsigned long long bk;
+        int p;
+        wave_first(key, row, bk, p);
+        if (key != 0 && row == p) {
+#pragma unroll
+            for (int s = 0; s < RP; ++s)
+                if (RP == 1 || tid + nt * s == p)
+#pragma unroll
+                    for (int k = 0; k < GJ_P; ++k) cand[buf][wave][k] = T[s][k];
+            cand[buf][wave][GJ_P] = own_inv;
+        }
+        if (lane == 0) {
+            ckey[buf][wave] = bk;
+            crow[buf][wave] = p;
+        }
+        __syncthreads();
+        // the best of the offers (the lowest row of equal ones), in every wavefront
+        bk = ckey[buf][0];
+        p = crow[buf][0];
+        for (int w = 1; w < waves; ++w) {
+            const unsigned long long kw = ckey[buf][w];
+            const int rw = crow[buf][w];
+            const bool take = kw > bk || (kw == bk && rw < p);
+            bk = take ? kw : bk;
+            p = take ? rw : p;
+        }
+        p = __builtin_amdgcn_readfirstlane(p);
+        bad = bad || !(__longlong_as_double((long long)bk) > 1e-300);   // uniform; the rest of the steps is dropped
+        p = p < m ? p : 0;
+        const int win = (RP == 1 ? p : p & (NT - 1)) >> 6;              // (RP > 1: all NT threads)
+        double u[GJ_P];
+        const double iv = cand[buf][win][GJ_P];
+#pragma unroll
+        for (int k = 0; k < GJ_P; ++k) u[k] = (k == q ? 1.0 : cand[buf][win][k]) * iv;
+#pragma unroll
+        for (int s = 0; s < RP; ++s) {
+            const int r = tid + nt * s;
+            const double fq = T[s][q];
+            f[s][q] = fq;
+            const bool is_p = r == p;
+#pragma unroll
+            for (int k = 0; k < GJ_P; ++k) {
+                const double t = fma(-fq, u[k], k == q ? 0.0 : T[s][k]);
+                T[s][k] = is_p ? u[k] : t;
+            }
+            if (is_p) {
+                step[s] = c0 + q;
+                my_inv[s] = iv;
+            }
         }
     }
+    if (bad) {   // uniform over the block
+        if (tid == 0) *B.singular = 1;
+        return;
+    }
+    // written at the end: a store before a barrier is waited for at it
+#pragma unroll
+    for (int s = 0; s < RP; ++s) {
+        const int r = tid + nt * s;
+        if (r >= m) continue;
+#pragma unroll
+        for (int k = 0; k < GJ_P; ++k) {
+            B.F[(int64_t)r * GJ_P + k] = f[s][k];
+            if (k < nq) B.W[(int64_t)r * m + c0 + k] = T[s][k];
+        }
+        if (step[s] >= c0) {
+            B.step[r] = step[s];
+            B.at[step[s]] = r;
+            B.piv[step[s] - c0] = r;
+            B.inv[step[s] - c0] = my_inv[s];
+        }
+    }
+    if (tid >= nq && tid < GJ_P) {   // steps past the last column
+        B.piv[tid] = 0;
+        B.inv[tid] = 0.0;
+    }
+}
+
+__global__ __launch_bounds__(256) void gj_apply(int m, int c0, GJBuf B) {
+    __shared__ double fp[GJ_P][GJ_P + 1];             // f of step t on the pivot row of step q
+    __shared__ double U[GJ_P][16], E[GJ_P][16];       // the pivot rows: as each step uses them; after the panel
+    __shared__ double fs[256][GJ_P + 1];
+    static_assert(GJ_P == 16, "a block's columns are one panel's");
+    const int j0 = blockIdx.x * 16;
+    if (j0 == c0 || *B.singular) return;              // the panel's own columns are done
+    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4, col = j0 + tx;
+    const bool on = col < m;
+    const int pr = B.piv[ty];
+    fp[tx][ty] = B.F[(int64_t)pr * GJ_P + tx];
+    U[ty][tx] = on ? B.W[(int64_t)pr * m + col] : 0.0;
+    __syncthreads();
+    if (tid < 16) {
+        double u[GJ_P];
+#pragma unroll
+        for (int q = 0; q < GJ_P; ++q) {
+            u[q] = U[q][tid];
+#pragma unroll
+            for (int t = 0; t < q; ++t) u[q] = fma(-fp[t][q], u[t], u[q]);
+            u[q] *= B.inv[q];
+        }
+#pragma unroll
+        for (int q = 0; q < GJ_P; ++q) {
+            U[q][tid] = u[q];
+            double v = u[q];
+#pragma unroll
+            for (int t = q + 1; t < GJ_P; ++t) v = fma(-fp[t][q], u[t], v);
+            E[q][tid] = v;
+        }
+    }
+    __syncthreads();
+    double u[GJ_P];
+#pragma unroll
+    for (int q = 0; q < GJ_P; ++q) u[q] = U[q][tx];
+    for (int r0 = 0; r0 < m; r0 += 256) {   // 256 rows at a time, 16 to a thread
+        double v[16];
+        int st[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int r = r0 + ty + 16 * i;
+            v[i] = on && r < m ? B.W[(int64_t)r * m + col] : 0.0;
+            st[i] = r < m ? B.step[r] : -1;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int r = r0 + ty + 16 * i;
+            fs[ty + 16 * i][tx] = r < m ? B.F[(int64_t)r * GJ_P + tx] : 0.0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int r = r0 + ty + 16 * i;
+#pragma unroll
+            for (int q = 0; q < GJ_P; ++q) v[i] = fma(-fs[ty + 16 * i][q], u[q], v[i]);
+            if (st[i] >= c0 && st[i] < c0 + GJ_P) v[i] = E[st[i] - c0][tx];
+            if (on && r < m) B.W[(int64_t)r * m + col] = v[i];
+        }
+    }
+}
+
+// step s is row at[s]; column k of the rows belongs to row at[k]
+__global__ void gj_extract(int m, GJBuf B, double *Ainv) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= (int64_t)m * m || *B.singular) return;
+    const int r = (int)(e / m), k = (int)(e % m);
+    Ainv[(int64_t)B.step[r] * m + B.at[k]] = B.W[e];
+}
+
+// ---- MaxVol (FP64) ----------------------------------------------------------
+// C = cand A^-1 and A^-1 are updated row by row, so a block owns rows: rows
+// [0, n) are C's, [n, n + m) A^-1's, MV_ROWS or more to a block.  Every launch is one
+// swap: each block finds the largest |C| from the blocks' partial maxima of
+// the launch before (the same search in every block: no grid-wide exchange),
+// takes the pivot row from the copy the block that owns it left, updates its
+// rows and leaves the maximum of its own and a copy of the row that holds it.
+// The partial maxima and the copies are double-buffered, since a launch reads
+// one set while writing the next.  Bound by the launch turnaround and one
+// chain of dependent loads (5 us a swap at 300 candidates, m = 212; six
+// launches, one of them a serial search of 256 partials, took 47 us).
+struct MVState {
+    int32_t done, swaps;
+};
+constexpr int MV_T = 256, MV_ROWS = 4, MV_BLOCKS = 512;
+
+struct MVBuf {
+    double *C;          // [n][m]
+    double *pv[2];      // [blocks] largest |C| of a block's rows (-1: none)
+    int64_t *pi[2];     // [blocks] its flat index
+    double *row[2];     // [blocks][m] the row it lies in
+    MVState *st;
+    int blocks, rpb;    // blocks, rows per block (of the n + m)
+};
+
+// a before b: larger value, lower index on ties
+__device__ inline bool mv_before(double v, int64_t i, double bv, int64_t bi) { return v > bv || (v == bv && i < bi); }
+
+// the block's largest (v, i) in every thread
+__device__ inline void mv_block_max(double &v, int64_t &i) {
+    __shared__ double sv[MV_T / 64];
+    __shared__ int64_t si[MV_T / 64];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const double ov = __shfl_xor(v, o, 64);
+        const int64_t oi = __shfl_xor(i, o, 64);
+        if (mv_before(ov, oi, v, i)) {
+            v = ov;
+            i = oi;
+        }
+    }
+    __syncthreads();   // sv / si of a call before are read, the block's stores are visible to it
+    if ((threadIdx.x & 63) == 0) {
+        sv[threadIdx.x >> 6] = v;
+        si[threadIdx.x >> 6] = i;
+    }
+    __syncthreads();
+    v = sv[0];
+    i = si[0];
+    for (int w = 1; w < MV_T / 64; ++w)
+        if (mv_before(sv[w], si[w], v, i)) {
+            v = sv[w];
+            i = si[w];
+        }
+}
+
+constexpr int64_t MV_NONE = 0x7fffffffffffffffLL;
+// leaves the block's maximum and a copy of its row for the next launch
+__device__ inline void mv_leave(const MVBuf &B, int par, int m, double bv, int64_t bi) {
+    mv_block_max(bv, bi);
+    if (threadIdx.x == 0) {
+        B.pv[par][blockIdx.x] = bv;
+        B.pi[par][blockIdx.x] = bi;
+    }
+    if (bi == MV_NONE) return;
+    const double *src = B.C + bi / m * m;
+    double *dst = B.row[par] + (int64_t)blockIdx.x * m;
+    for (int k = threadIdx.x; k < m; k += MV_T) dst[k] = src[k];
+}
+
+// C = X A^-1 (plain FP64 sums over k in order) and the first partial maxima
+__global__ __launch_bounds__(MV_T) void mv_start(const double *X, int64_t n, const double *Ainv, int m, MVBuf B) {
+    constexpr int RC = 4, KT = 256;   // rows at a time, k tile
+    __shared__ double xs[RC][KT];
+    if (blockIdx.x == 0 && threadIdx.x == 0) *B.st = MVState{0, 0};
+    const int64_t r0 = (int64_t)blockIdx.x * B.rpb, r1 = r0 + B.rpb < n ? r0 + B.rpb : n;
+    double bv = -1.0;
+    int64_t bi = MV_NONE;
+    for (int64_t r = r0; r < r1; r += RC) {
+        const int nr = r1 - r < RC ? (int)(r1 - r) : RC;
+        for (int j0 = 0; j0 < m; j0 += MV_T) {
+            const int j = j0 + threadIdx.x;
+            double s[RC] = {0.0, 0.0, 0.0, 0.0};
+            for (int k0 = 0; k0 < m; k0 += KT) {
+                __syncthreads();
+#pragma unroll
+                for (int q = 0; q < RC; ++q)
+                    xs[q][threadIdx.x] = q < nr && k0 + (int)threadIdx.x < m ? X[(r + q) * m + k0 + threadIdx.x] : 0.0;
+                __syncthreads();
+                const int nk = m - k0 < KT ? m - k0 : KT;
+                if (j < m)
+#pragma unroll 16
+                    for (int kk = 0; kk < nk; ++kk) {
+                        const double a = Ainv[(int64_t)(k0 + kk) * m + j];
+#pragma unroll
+                        for (int e = 0; e < RC; ++e) s[e] = fma(xs[e][kk], a, s[e]);
+                    }
+            }
+            if (j < m)
+#pragma unroll
+                for (int e = 0; e < RC; ++e)
+                    if (e < nr) {
+                        const int64_t at = (r + e) * m + j;
+                        B.C[at] = s[e];
+                        if (mv_before(fabs(s[e]), at, bv, bi)) {
+                            bv = fabs(s[e]);
+                            bi = at;
+                        }
+                    }
+        }
+    }
+    mv_leave(B, 0, m, bv, bi);
+}
+static_assert(MV_T == 256, "mv_start stages one k tile of a row with one thread per entry");
+
+// the wavefront's largest value (-1: none), its lowest index and that lane's
+// tag: the high words by DPP, then the few lanes that hold it (usually one)
+__device__ inline void mv_wave_max(double &v, int64_t &i, int &tag) {
+    const unsigned long long key = i != MV_NONE ? (unsigned long long)__double_as_longlong(v) : 0ull;
+    const uint32_t hi = wave_max_u32((uint32_t)(key >> 32));
+    unsigned long long have = __ballot(i != MV_NONE && (uint32_t)(key >> 32) == hi);
+    double bv = -1.0;
+    int64_t bi = MV_NONE;
+    int bt = 0;
+    while (have) {
+        const int l = __ffsll(have) - 1;
+        const double lv = lane_value(v, l);
+        const int64_t li = ((int64_t)__builtin_amdgcn_readlane((int)(i >> 32), l) << 32) |
+                           (uint32_t)__builtin_amdgcn_readlane((int)i, l);
+        const int lt = __builtin_amdgcn_readlane(tag, l);
+        if (mv_before(lv, li, bv, bi)) {
+            bv = lv;
+            bi = li;
+            bt = lt;
+        }
+        have &= have - 1;
+    }
+    v = bv;
+    i = bi;
+    tag = bt;
+}
+
+// One swap when a block's rows fit its threads' registers (m <= MV_T, at most
+// MV_ROWS rows to a block): its rows are loaded beside the partial maxima,
+// every wavefront finds the pivot by itself (DPP maximum, no barrier), and
+// the row the block leaves comes from the registers.
+__global__ __launch_bounds__(MV_T) void mv_swap_small(int64_t n, int m, double thr, int it, MVBuf B, double *Ainv,
+                                                      double *A, double *cand, int32_t *swap_cand, int32_t *swap_col) {
+    __shared__ double colv[MV_ROWS], sv[MV_T / 64];
+    __shared__ int64_t si[MV_T / 64];
+    const int k = threadIdx.x, lane = threadIdx.x & 63, par = it & 1;
+    const bool on = k < m;
+    const int64_t r0 = (int64_t)blockIdx.x * B.rpb;
+    double x[MV_ROWS];
+    double *at[MV_ROWS];
+#pragma unroll
+    for (int e = 0; e < MV_ROWS; ++e) {
+        const int64_t q = r0 + e;
+        at[e] = e < B.rpb && q < n + m && on ? (q < n ? B.C + q * m + k : Ainv + (q - n) * m + k) : nullptr;
+        x[e] = at[e] ? *at[e] : 0.0;
+    }
+    constexpr int PB = MV_BLOCKS / 64;
+    double bv = -1.0;
+    int64_t bi = MV_NONE;
+    int win = 0;
+#pragma unroll
+    for (int u = 0; u < PB; ++u) {
+        const int b = u * 64 + lane;
+        if (b < B.blocks) {
+            const double v = B.pv[par][b];
+            const int64_t i = B.pi[par][b];
+            if (mv_before(v, i, bv, bi)) {
+                bv = v;
+                bi = i;
+                win = b;
+            }
+        }
+    }
+    if (B.st->done) return;
+    mv_wave_max(bv, bi, win);
+    if (!(bv > thr)) {   // the same in every wavefront and block
+        if (blockIdx.x == 0 && threadIdx.x == 0) B.st->done = 1;
+        return;
+    }
+    const double *crow = B.row[par] + (int64_t)win * m;
+    const int64_t pi = bi / m;
+    const int pj = (int)(bi - pi * m);
+    const double piv = crow[pj], c = on ? crow[k] : 0.0;
+    if (k == pj)
+#pragma unroll
+        for (int e = 0; e < MV_ROWS; ++e) colv[e] = x[e];
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) {
+            swap_cand[it] = (int32_t)pi;
+            swap_col[it] = pj;
+            B.st->swaps = it + 1;
+        }
+        if (on) {
+            const double t = A[(int64_t)pj * m + k];
+            A[(int64_t)pj * m + k] = cand[pi * m + k];
+            cand[pi * m + k] = t;
+        }
+    }
+    const double v = (c - (k == pj ? 1.0 : 0.0)) / piv;
+    __syncthreads();
+    bv = -1.0;
+    bi = MV_NONE;
+#pragma unroll
+    for (int e = 0; e < MV_ROWS; ++e) {
+        const int64_t q = r0 + e;
+        x[e] = q == pi ? (k == pj ? 1.0 : 0.0) - v : x[e] - colv[e] * v;
+        if (at[e]) {
+            *at[e] = x[e];
+            if (q < n && fabs(x[e]) > bv) {   // rows in order: the lowest index of equal values
+                bv = fabs(x[e]);
+                bi = q * m + k;
+            }
+        }
+    }
+    int tag = 0;
+    mv_wave_max(bv, bi, tag);
     if (lane == 0) {
-        sv[wave] = bv;
-        si[wave] = bi;
+        sv[threadIdx.x >> 6] = bv;
+        si[threadIdx.x >> 6] = bi;
     }
     __syncthreads();
     bv = sv[0];
     bi = si[0];
-    for (int w = 1; w < GJ_T / 64; ++w)
-        if (sv[w] > bv || (sv[w] == bv && si[w] < bi)) {
+#pragma unroll
+    for (int w = 1; w < MV_T / 64; ++w)
+        if (mv_before(sv[w], si[w], bv, bi)) {
             bv = sv[w];
             bi = si[w];
         }
-    if (!(bv > 1e-300)) {
-        if (r == 0 && tid == 0) *singular = 1;
-        return;   // uniform over the block
+    if (threadIdx.x == 0) {
+        B.pv[par ^ 1][blockIdx.x] = bv;
+        B.pi[par ^ 1][blockIdx.x] = bi;
     }
-    const int p = bi;
-    const double *prow = cur + (int64_t)p * n2;
-    const double inv = 1.0 / prow[c];
-    double *out = next + (int64_t)r * n2;
-    if (r == c) {
-        for (int k = tid; k < n2; k += GJ_T) out[k] = k == c ? 1.0 : prow[k] * inv;
-        return;
-    }
-    const double *src = cur + (int64_t)(r == p ? c : r) * n2;
-    const double f = src[c];
-    for (int k = tid; k < n2; k += GJ_T) out[k] = k == c ? 0.0 : fma(-f, prow[k] * inv, src[k]);
+    if (bi == MV_NONE || !on) return;
+    const int64_t best = bi / m - r0;
+#pragma unroll
+    for (int e = 0; e < MV_ROWS; ++e)
+        if (e == best) B.row[par ^ 1][(int64_t)blockIdx.x * m + k] = x[e];
 }
 
-__global__ void gj_setup(const double *A, int m, double *W) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (int64_t)m * 2 * m) return;
-    const int r = (int)(e / (2 * m)), k = (int)(e % (2 * m));
-    W[e] = k < m ? A[(int64_t)r * m + k] : (k - m == r ? 1.0 : 0.0);
-}
-
-__global__ void gj_extract(const double *W, int m, double *Ainv) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (int64_t)m * m) return;
-    const int r = (int)(e / m), k = (int)(e % m);
-    Ainv[e] = W[(int64_t)r * 2 * m + m + k];
-}
-
-// ---- MaxVol (FP64) ----------------------------------------------------------
-// C = cand * Ainv (plain FP64, one thread per entry)
-__global__ void gemm_f64(const double *X, int64_t n, const double *Ainv, int m, double *C) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n * m) return;
-    const int64_t i = e / m;
-    const int j = (int)(e % m);
-    double s = 0.0;
-    for (int k = 0; k < m; ++k) s = fma(X[i * m + k], Ainv[(int64_t)k * m + j], s);
-    C[e] = s;
-}
-
-struct MVState {
-    int32_t done, swaps, i, j;
-    double piv;
-};
-
-constexpr int AM_T = 256;
-__global__ void absmax_partial(const double *C, int64_t total, double *pv, int64_t *pi) {
-    __shared__ double sv[AM_T];
-    __shared__ int64_t si[AM_T];
+// swap number `it` (par = it & 1): j, i = the largest |C|; v = (C[i] - e_j) / C[i][j];
+// C[r] -= C[r][j] v, C[i] = e_j - v, A^-1[r] -= A^-1[r][j] v; A[j] <-> cand[i]
+__global__ __launch_bounds__(MV_T) void mv_swap(int64_t n, int m, double thr, int it, MVBuf B, double *Ainv, double *A,
+                                                double *cand, int32_t *swap_cand, int32_t *swap_col) {
+    constexpr int RC = 8;
+    __shared__ double colv[RC];
+    __shared__ int s_win;
+    if (B.st->done) return;   // written by an earlier launch, or by block 0 of this one, which stops as well
+    const int par = it & 1;
     double bv = -1.0;
-    int64_t bi = 0x7fffffffffffffffLL;
-    for (int64_t e = (int64_t)blockIdx.x * AM_T + threadIdx.x; e < total; e += (int64_t)gridDim.x * AM_T) {
-        const double v = fabs(C[e]);
-        if (v > bv || (v == bv && e < bi)) {
+    int64_t bi = MV_NONE;
+    int win = 0;
+    for (int b = threadIdx.x; b < B.blocks; b += MV_T) {
+        const double v = B.pv[par][b];
+        const int64_t i = B.pi[par][b];
+        if (mv_before(v, i, bv, bi)) {
             bv = v;
-            bi = e;
+            bi = i;
+            win = b;
         }
     }
-    sv[threadIdx.x] = bv;
-    si[threadIdx.x] = bi;
+    const int64_t mine = bi;
+    mv_block_max(bv, bi);
+    if (mine == bi && bi != MV_NONE) s_win = win;   // indices are unique: one thread
     __syncthreads();
-    for (int w = AM_T / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) {
-            const double ov = sv[threadIdx.x + w];
-            const int64_t oi = si[threadIdx.x + w];
-            if (ov > sv[threadIdx.x] || (ov == sv[threadIdx.x] && oi < si[threadIdx.x])) {
-                sv[threadIdx.x] = ov;
-                si[threadIdx.x] = oi;
-            }
+    if (!(bv > thr)) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) B.st->done = 1;
+        return;
+    }
+    const double *crow = B.row[par] + (int64_t)s_win * m;
+    const int64_t pi = bi / m;
+    const int pj = (int)(bi - pi * m);
+    const double piv = crow[pj];
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) {
+            swap_cand[it] = (int32_t)pi;
+            swap_col[it] = pj;
+            B.st->swaps = it + 1;
+        }
+        for (int k = threadIdx.x; k < m; k += MV_T) {
+            const double t = A[(int64_t)pj * m + k];
+            A[(int64_t)pj * m + k] = cand[pi * m + k];
+            cand[pi * m + k] = t;
+        }
+    }
+    const int64_t r0 = (int64_t)blockIdx.x * B.rpb, r1 = r0 + B.rpb < n + m ? r0 + B.rpb : n + m;
+    bv = -1.0;
+    bi = MV_NONE;
+    for (int64_t r = r0; r < r1; r += RC) {
+        const int nr = r1 - r < RC ? (int)(r1 - r) : RC;
+        __syncthreads();   // the chunk before is done with colv
+        if ((int)threadIdx.x < nr) {
+            const int64_t q = r + threadIdx.x;
+            colv[threadIdx.x] = q < n ? B.C[q * m + pj] : Ainv[(q - n) * m + pj];
         }
         __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        pv[blockIdx.x] = sv[0];
-        pi[blockIdx.x] = si[0];
-    }
-}
-
-__global__ void absmax_final(const double *pv, const int64_t *pi, int nb, int m, double thr, int max_swaps,
-                             const double *C, MVState *st, int32_t *swap_cand, int32_t *swap_col) {
-    if (threadIdx.x != 0) return;
-    if (st->done) return;
-    double bv = -1.0;
-    int64_t bi = 0x7fffffffffffffffLL;
-    for (int b = 0; b < nb; ++b)
-        if (pv[b] > bv || (pv[b] == bv && pi[b] < bi)) {
-            bv = pv[b];
-            bi = pi[b];
+        for (int k = threadIdx.x; k < m; k += MV_T) {
+            const double v = (crow[k] - (k == pj ? 1.0 : 0.0)) / piv;
+#pragma unroll
+            for (int e = 0; e < RC; ++e) {
+                if (e >= nr) continue;
+                const int64_t q = r + e;
+                double *x = q < n ? B.C + q * m + k : Ainv + (q - n) * m + k;
+                const double y = q == pi ? (k == pj ? 1.0 : 0.0) - v : *x - colv[e] * v;
+                *x = y;
+                if (q < n && mv_before(fabs(y), q * m + k, bv, bi)) {
+                    bv = fabs(y);
+                    bi = q * m + k;
+                }
+            }
         }
-    if (!(bv > thr) || st->swaps >= max_swaps) {
-        st->done = 1;
-        return;
     }
-    st->i = (int32_t)(bi / m);
-    st->j = (int32_t)(bi % m);
-    st->piv = C[bi];
-    swap_cand[st->swaps] = st->i;
-    swap_col[st->swaps] = st->j;
-}
-
-// save the pivot row of C and the pivot columns of C and A^-1
-__global__ void mv_save(const double *C, int64_t n, const double *Ainv, int m, const MVState *st, double *crow,
-                        double *ccol, double *acol) {
-    if (st->done) return;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < m) {
-        crow[t] = C[(int64_t)st->i * m + t];
-        acol[t] = Ainv[t * m + st->j];
-    }
-    if (t < n) ccol[t] = C[t * m + st->j];
-}
-
-// C <- C - C[:,j] (c - e_j) / c_j; row i becomes the replaced row's coordinates
-// e_j - (c - e_j) / c_j.  A^-1 <- A^-1 - A^-1[:,j] (c - e_j) / c_j.
-__global__ void mv_update(double *C, int64_t n, double *Ainv, int m, const MVState *st, const double *crow,
-                          const double *ccol, const double *acol) {
-    if (st->done) return;
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int j = st->j, i = st->i;
-    const double pv = st->piv;
-    if (e < n * m) {
-        const int64_t r = e / m;
-        const int k = (int)(e % m);
-        const double v = (crow[k] - (k == j ? 1.0 : 0.0)) / pv;
-        if (r == i) C[e] = (k == j ? 1.0 : 0.0) - v;
-        else C[e] = C[e] - ccol[r] * v;
-    }
-    if (e < (int64_t)m * m) {
-        const int64_t r = e / m;
-        const int k = (int)(e % m);
-        const double v = (crow[k] - (k == j ? 1.0 : 0.0)) / pv;
-        Ainv[e] = Ainv[e] - acol[r] * v;
-    }
-}
-
-// exchange the rows: A[j] <-> cand[i]
-__global__ void mv_swap(double *A, double *cand, int m, MVState *st) {
-    if (st->done) return;
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < m) {
-        const double t = A[(int64_t)st->j * m + k];
-        A[(int64_t)st->j * m + k] = cand[(int64_t)st->i * m + k];
-        cand[(int64_t)st->i * m + k] = t;
-    }
-}
-
-__global__ void mv_count(MVState *st) {
-    if (threadIdx.x == 0 && !st->done) st->swaps += 1;
-}
-
-__global__ void mv_init(MVState *st) {
-    if (threadIdx.x == 0) {
-        st->done = 0;
-        st->swaps = 0;
-        st->i = st->j = 0;
-        st->piv = 0.0;
-    }
+    mv_leave(B, par ^ 1, m, bv, bi);
 }
 
 }  // namespace
@@ -1017,8 +1401,7 @@ void prepare_split(ActiveSet &as, hipStream_t st) {
     as.s8.ensure((size_t)GI_SL * as.CP8 * as.KP8);
     as.fexp.ensure(sizeof(int32_t) * as.CP8);
     as.dsc.ensure(sizeof(double) * as.KP8);
-    hipLaunchKernelGGL(i8_colscale, dim3((unsigned)((as.KP8 + 255) / 256)), dim3(256), 0, st, as.A.as<double>(), m,
-                       as.KP8, as.dsc.as<double>());
+    hipLaunchKernelGGL(i8_colscale, dim3((unsigned)as.KP8), dim3(64), 0, st, as.A.as<double>(), m, as.dsc.as<double>());
     hipLaunchKernelGGL(i8_slice_ainv, dim3((unsigned)as.CP8), dim3(256), 0, st, as.Ainv.as<double>(), m, as.KP8,
                        as.CP8, as.dsc.as<double>(), as.s8.as<int8_t>(), as.fexp.as<int32_t>());
     if (m <= 32 * GR_NK_MAX) {   // A^-1 in the lane order of the FP64 product
@@ -1280,19 +1663,31 @@ double mfma_rate(int kind, int iters, hipStream_t st) {
 
 void launch_invert(ActiveSet &as, const double *A, hipStream_t st, DevBuf &work, int *singular_host) {
     const int m = as.m;
-    const size_t wsz = (size_t)2 * m * m;
-    work.ensure(sizeof(double) * 2 * wsz + 64);
-    double *W[2] = {work.as<double>(), work.as<double>() + wsz};
-    int32_t *flag = reinterpret_cast<int32_t *>(W[1] + wsz);
-    launch_zero(flag, sizeof(int32_t), st);
-    const int64_t tot = (int64_t)wsz;
-    hipLaunchKernelGGL(gj_setup, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, A, m, W[0]);
-    for (int c = 0; c < m; ++c)
-        hipLaunchKernelGGL(gj_step, dim3((unsigned)m), dim3(GJ_T), 0, st, W[c & 1], W[(c + 1) & 1], m, c, flag);
-    hipLaunchKernelGGL(gj_extract, dim3((unsigned)(((int64_t)m * m + 255) / 256)), dim3(256), 0, st, W[m & 1], m,
-                       as.Ainv.as<double>());
+    MTP_CHECK(m <= 4 * GJ_T, MTP_E_INVAL, "active set: at most 4096 columns");
+    const size_t mm = (size_t)m * m;
+    work.ensure(sizeof(double) * (mm + (size_t)m * GJ_P + GJ_P) + sizeof(int32_t) * (2 * (size_t)m + GJ_P + 1));
+    GJBuf B{};
+    B.W = work.as<double>();
+    B.F = B.W + mm;
+    B.inv = B.F + (size_t)m * GJ_P;
+    B.piv = reinterpret_cast<int32_t *>(B.inv + GJ_P);
+    B.step = B.piv + GJ_P;
+    B.at = B.step + m;
+    B.singular = B.at + m;
+    const dim3 ge((unsigned)((mm + 255) / 256));
+    hipLaunchKernelGGL(gj_setup, ge, dim3(256), 0, st, A, m, B);
+    const unsigned nt = (unsigned)((m + 63) / 64 * 64);
+    for (int c0 = 0; c0 < m; c0 += GJ_P) {
+        if (m <= 256) hipLaunchKernelGGL((gj_panel<1, 256>), dim3(1), dim3(nt), 0, st, m, c0, B);
+        else if (m <= 512) hipLaunchKernelGGL((gj_panel<1, 512>), dim3(1), dim3(nt), 0, st, m, c0, B);
+        else if (m <= GJ_T) hipLaunchKernelGGL((gj_panel<2, 512>), dim3(1), dim3(512), 0, st, m, c0, B);
+        else if (m <= 2 * GJ_T) hipLaunchKernelGGL((gj_panel<4, 512>), dim3(1), dim3(512), 0, st, m, c0, B);
+        else hipLaunchKernelGGL((gj_panel<4, GJ_T>), dim3(1), dim3(GJ_T), 0, st, m, c0, B);
+        hipLaunchKernelGGL(gj_apply, dim3((unsigned)((m + 15) / 16)), dim3(256), 0, st, m, c0, B);
+    }
+    hipLaunchKernelGGL(gj_extract, ge, dim3(256), 0, st, m, B, as.Ainv.as<double>());
     int32_t h = 0;
-    MTP_HIP(hipMemcpyAsync(&h, flag, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    MTP_HIP(hipMemcpyAsync(&h, B.singular, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     MTP_HIP(hipStreamSynchronize(st));
     *singular_host = h;
 }
@@ -1300,46 +1695,39 @@ void launch_invert(ActiveSet &as, const double *A, hipStream_t st, DevBuf &work,
 void run_maxvol(ActiveSet &as, double *cand, int64_t n_cand, double thr, int max_swaps, int32_t *swap_cand,
                 int32_t *swap_col, int32_t *n_swaps, hipStream_t st, DevBuf &work) {
     const int m = as.m;
-    const int NB = 256;
-    const size_t need = sizeof(double) * ((size_t)n_cand * m + 2 * (size_t)m + (size_t)n_cand + NB) +
-                        sizeof(int64_t) * NB + sizeof(MVState) + 256;
-    work.ensure(need);
-    char *base = static_cast<char *>(work.ptr);
-    double *C = reinterpret_cast<double *>(base);
-    double *crow = C + (size_t)n_cand * m;
-    double *acol = crow + m;
-    double *ccol = acol + m;
-    double *pv = ccol + n_cand;
-    int64_t *pi = reinterpret_cast<int64_t *>(pv + NB);
-    MVState *state = reinterpret_cast<MVState *>(pi + NB);
-    hipLaunchKernelGGL(mv_init, dim3(1), dim3(64), 0, st, state);
-    const int64_t tot = n_cand * m;
-    if (tot > 0)
-        hipLaunchKernelGGL(gemm_f64, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, cand, n_cand,
-                           as.Ainv.as<double>(), m, C);
-    const int64_t upd = tot > (int64_t)m * m ? tot : (int64_t)m * m;
-    const int64_t sv = n_cand > m ? n_cand : m;
-    int nb = (int)((tot + AM_T - 1) / AM_T);
-    nb = nb < 1 ? 1 : (nb > NB ? NB : nb);
+    const int64_t rows = n_cand + m;
+    MVBuf B{};
+    B.blocks = (int)std::min<int64_t>((rows + MV_ROWS - 1) / MV_ROWS, MV_BLOCKS);
+    B.rpb = (int)((rows + B.blocks - 1) / B.blocks);
+    B.blocks = (int)((rows + B.rpb - 1) / B.rpb);
+    const size_t dbl = (size_t)n_cand * m + 2 * (size_t)B.blocks * (m + 1);
+    work.ensure(sizeof(double) * dbl + 2 * sizeof(int64_t) * B.blocks + sizeof(MVState) + 256);
+    double *p = work.as<double>();
+    B.C = p;
+    p += (size_t)n_cand * m;
+    for (int q = 0; q < 2; ++q) {
+        B.row[q] = p;
+        p += (size_t)B.blocks * m;
+        B.pv[q] = p;
+        p += B.blocks;
+    }
+    B.pi[0] = reinterpret_cast<int64_t *>(p);
+    B.pi[1] = B.pi[0] + B.blocks;
+    B.st = reinterpret_cast<MVState *>(B.pi[1] + B.blocks);
+    hipLaunchKernelGGL(mv_start, dim3((unsigned)B.blocks), dim3(MV_T), 0, st, cand, n_cand, as.Ainv.as<double>(), m, B);
+    // a block's rows in its threads' registers (2,048 rows of up to 256 columns), else through memory
+    const bool small = m <= MV_T && B.rpb <= MV_ROWS;
     MVState hs{};
-    for (int it = 0; it < max_swaps && tot > 0; ++it) {
-        hipLaunchKernelGGL(absmax_partial, dim3(nb), dim3(AM_T), 0, st, C, tot, pv, pi);
-        hipLaunchKernelGGL(absmax_final, dim3(1), dim3(64), 0, st, pv, pi, nb, m, thr, max_swaps, C, state, swap_cand,
-                           swap_col);
-        hipLaunchKernelGGL(mv_save, dim3((unsigned)((sv + 255) / 256)), dim3(256), 0, st, C, n_cand,
-                           as.Ainv.as<double>(), m, state, crow, ccol, acol);
-        hipLaunchKernelGGL(mv_update, dim3((unsigned)((upd + 255) / 256)), dim3(256), 0, st, C, n_cand,
-                           as.Ainv.as<double>(), m, state, crow, ccol, acol);
-        hipLaunchKernelGGL(mv_swap, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, as.A.as<double>(), cand, m,
-                           state);
-        hipLaunchKernelGGL(mv_count, dim3(1), dim3(64), 0, st, state);
+    for (int it = 0; it < max_swaps; ++it) {
+        hipLaunchKernelGGL(small ? mv_swap_small : mv_swap, dim3((unsigned)B.blocks), dim3(MV_T), 0, st, n_cand, m, thr,
+                           it, B, as.Ainv.as<double>(), as.A.as<double>(), cand, swap_cand, swap_col);
         if ((it & 31) == 31) {   // stop enqueueing once converged
-            MTP_HIP(hipMemcpyAsync(&hs, state, sizeof(MVState), hipMemcpyDeviceToHost, st));
+            MTP_HIP(hipMemcpyAsync(&hs, B.st, sizeof(MVState), hipMemcpyDeviceToHost, st));
             MTP_HIP(hipStreamSynchronize(st));
             if (hs.done) break;
         }
     }
-    MTP_HIP(hipMemcpyAsync(&hs, state, sizeof(MVState), hipMemcpyDeviceToHost, st));
+    MTP_HIP(hipMemcpyAsync(&hs, B.st, sizeof(MVState), hipMemcpyDeviceToHost, st));
     MTP_HIP(hipStreamSynchronize(st));
     *n_swaps = hs.swaps;
     prepare_split(as, st);
