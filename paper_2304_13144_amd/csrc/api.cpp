@@ -338,7 +338,7 @@ void evaluate(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb, int p
         double *gam = o.gamma ? o.gamma : static_cast<double *>(ws.get(m->gamma_ws, sizeof(double) * n));
         int32_t *blk = nullptr;
         const int sched = grade_sched_for(m, n, prec, o.mode);
-        const int count_rows = grade_count_rows(m->act[o.mode], prec, sched);
+        const int count_rows = grade_count_rows(m->act[o.mode], prec, sched, n);
         if (want_sel)
             blk = static_cast<int32_t *>(
                 ws.get(m->selblk, sizeof(int32_t) * (size_t)((n + count_rows - 1) / count_rows + 1)));
@@ -1378,7 +1378,7 @@ int mtp_tune(mtp_model *m, const mtp_system *s, const mtp_nbrs *nb, mtp_precisio
         const int ldb = ld_of(m->m_of(g), p);
         const double *rows = m->brow.as<double>();
         int cr = GRADE_ROWS;   // the finest preselection count among the forms
-        for (int sc : cand) cr = std::min(cr, grade_count_rows(m->act[g], p, sc));
+        for (int sc : cand) cr = std::min(cr, grade_count_rows(m->act[g], p, sc, n));
         DevBuf blk;
         blk.ensure(sizeof(int32_t) * (size_t)((n + cr - 1) / cr + 1));
         constexpr int GREPS = 10;

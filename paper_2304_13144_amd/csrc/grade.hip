@@ -533,6 +533,108 @@ __global__ __launch_bounds__(512) void grade_f64_kouter(const double *__restrict
     }
 }
 
+// The k-outer product for few rows: 16 RG rows per block (RG = 1 or 2 row
+// groups), the column tiles dealt out to the 8 / RG wavefronts of each row
+// group, so that launches of up to 8,192 rows still give every CU a block.
+// The rows (all k) are staged in LDS once; each wavefront streams its own
+// tiles of A^-1 from L2 in the lane order of f64_stage_ainv, one chunk of
+// eight k steps ahead of the products (tiles are not shared inside a row
+// group, so LDS would not save their loads).  The same products in the same
+// order as grade_f64_kouter: the grades are the same bit for bit.  Bound by
+// the FP64 MFMAs of one block per CU (14 tiles x 53 steps on four SIMDs, 5.7
+// us) behind the first loads.  m = 212, back to back: 864 rows 12.8 us (34.0 in
+// 64-row blocks of 8 wavefronts, 21.9 in 32-row blocks), 4,096 rows 13.5 us,
+// 5,148 to 8,192 rows (RG = 2) 21.6 to 22.1 us (34.0; 22.2 to 22.6); above that
+// 64-row blocks (29.1 us at 8,256 and at 16,384 rows).
+template <int NK, int RG>
+__global__ __launch_bounds__(512) void grade_f64_few(const double *__restrict__ brow, int64_t ldn, int64_t n,
+                                                     const double *__restrict__ L, int m, double *gamma,
+                                                     int32_t *argmax, double thr, int32_t *sel_blk) {
+    constexpr int KS = 8 * NK, KC = 8, NCH = NK;           // k steps of four, per chunk, chunks
+    constexpr int ROWS = 16 * RG, WV = 8 / RG;             // rows; wavefronts per row group
+    constexpr int TP = (2 * NK + WV - 1) / WV;             // tiles per wavefront
+    __shared__ double sA[RG][32 * NK][16];
+    __shared__ double s_best[WV][ROWS];
+    __shared__ int s_idx[WV][ROWS];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int rg = wave % RG, tw = wave / RG;
+    const int lr = lane & 15, lk = lane >> 4;
+    const int64_t row0 = (int64_t)blockIdx.x * ROWS;
+    const int ntile = (m + 15) / 16, ksn = (m + 3) / 4;
+    double b[2][KC][TP];
+    auto fetch = [&](int c) {
+#pragma unroll
+        for (int s = 0; s < KC; ++s)
+#pragma unroll
+            for (int i = 0; i < TP; ++i) {
+                const int t = min(tw + WV * i, ntile - 1);   // past the last tile: an in-bounds tile, never compared
+                b[c & 1][s][i] = L[((int64_t)t * KS + KC * c + s) * 64 + lane];
+            }
+    };
+    fetch(0);
+    constexpr int ST = 32 * NK * ROWS / 512;   // staged values per thread (512 consecutive row entries at a time)
+#pragma unroll
+    for (int q = 0; q < ST; ++q) {
+        const int e = tid + 512 * q, r = e % ROWS, k = e / ROWS;
+        sA[r >> 4][k][r & 15] = brow[min(row0 + r, n - 1) + (int64_t)k * ldn];
+    }
+    __syncthreads();
+    doublex4 acc[TP];
+#pragma unroll
+    for (int i = 0; i < TP; ++i) acc[i] = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+        if (c + 1 < NCH) fetch(c + 1);
+#pragma unroll
+        for (int s = 0; s < KC; ++s) {
+            const double a = sA[rg][4 * (KC * c + s) + lk][lr];
+            if (KC * c + s <= 8 * (NK - 1) || KC * c + s < ksn)   // uniform (see grade_f64_kouter)
+#pragma unroll
+                for (int i = 0; i < TP; ++i)   // (a branch around the tiles past the last would end every load's flight)
+                    acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b[c & 1][s][i], acc[i], 0, 0, 0);
+        }
+    }
+    double best[4] = {-1.0, -1.0, -1.0, -1.0};
+    int bidx[4] = {0x7fffffff, 0x7fffffff, 0x7fffffff, 0x7fffffff};
+#pragma unroll
+    for (int i = 0; i < TP; ++i) {
+        const int col = 16 * (tw + WV * i) + lr;
+        if (col < m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) better(fabs(acc[i][r]), col, best[r], bidx[r]);
+    }
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const double ov = __shfl_xor(best[r], o, 64);
+            const int oc = __shfl_xor(bidx[r], o, 64);
+            better(ov, oc, best[r], bidx[r]);
+        }
+    if (lr == 0)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            s_best[tw][rg * 16 + lk + 4 * r] = best[r];
+            s_idx[tw][rg * 16 + lk + 4 * r] = bidx[r];
+        }
+    __syncthreads();
+    if (tid < 64) {   // wavefront 0: one row per lane
+        const int rr = tid < ROWS ? tid : ROWS - 1;
+        double bv = s_best[0][rr];
+        int bc = s_idx[0][rr];
+#pragma unroll
+        for (int w = 1; w < WV; ++w) better(s_best[w][rr], s_idx[w][rr], bv, bc);
+        const int64_t row = row0 + tid;
+        const bool live = tid < ROWS && row < n;
+        if (live) {
+            gamma[row] = bv;
+            if (argmax) argmax[row] = bc;
+        }
+        const unsigned long long sel = __ballot(live && bv > thr);
+        if (sel_blk && tid == 0) sel_blk[blockIdx.x] = __popcll(sel);
+    }
+}
+
 // A^-1 in the lane order of grade_f64: out[(tile * 8 NK + s) * 64 + l] =
 // A^-1[4 s + l / 16][16 tile + l % 16], zero past m
 __global__ void f64_stage_ainv(const double *Ainv, int m, int NK, int ntile, double *out) {
@@ -1462,6 +1564,18 @@ static void launch_grade_f64_kouter(const ActiveSet &as, const double *brow, int
                        as.m, gamma, argmax, thr, sel_blk);
 }
 
+template <int NK>
+static void launch_grade_few(int groups, const ActiveSet &as, const double *brow, int64_t ldn, int64_t n, double *gamma,
+                             int32_t *argmax, hipStream_t st, double thr, int32_t *sel_blk) {
+    const dim3 grid((unsigned)((n + 16 * groups - 1) / (16 * groups)));
+    if (groups == 1)
+        hipLaunchKernelGGL((grade_f64_few<NK, 1>), grid, dim3(512), 0, st, brow, ldn, n, as.lane64.as<double>(), as.m,
+                           gamma, argmax, thr, sel_blk);
+    else
+        hipLaunchKernelGGL((grade_f64_few<NK, 2>), grid, dim3(512), 0, st, brow, ldn, n, as.lane64.as<double>(), as.m,
+                           gamma, argmax, thr, sel_blk);
+}
+
 template <int KS>
 static void launch_grade_i8(const ActiveSet &as, const double *brow, int ldb, int64_t ldn, int64_t n, double *gamma,
                             int32_t *argmax, hipStream_t st, double thr, int32_t *sel_blk) {
@@ -1483,14 +1597,27 @@ bool grade_sched_valid(const ActiveSet &as, int precision, int sched) {
     }
 }
 
-static int grade_sched_resolve(const ActiveSet &as, int precision, int sched) {
+constexpr int GRADE_CUS = 256;   // CUs a launch should fill
+static int grade_sched_resolve(const ActiveSet &as, int precision, int sched, int64_t n) {
     if (sched != GRADE_AUTO) return sched;
     if (precision == MTP_MIXED && slice_product_fits(as.m)) return GRADE_I8;
-    return as.m <= 32 * GR_NK_MAX ? GRADE_F64_REG : GRADE_F64_LDS;
+    // k-outer: one block of 64 rows per CU with the long chunks, two per CU
+    // beyond (m = 212: 16,384 rows 29.8 against 30.2 us, 65,536 rows 118 against
+    // 104, 256,000 rows 454 against 407; rows held in registers 35, 142, 561)
+    if (as.m <= 32 * GR_NK_MAX) return n <= 64 * GRADE_CUS ? GRADE_F64_KOUTER : GRADE_F64_KOUTER2;
+    return GRADE_F64_LDS;
 }
 
-int grade_count_rows(const ActiveSet &as, int precision, int sched) {
-    return grade_sched_resolve(as, precision, sched) == GRADE_F64_PAIR ? GF2_ROWS : GRADE_ROWS;
+// row groups per block of the k-outer product on few rows, 0 when 64-row
+// blocks give every CU work enough
+static int few_groups(int64_t n, int sched) {
+    if (sched != GRADE_F64_KOUTER && sched != GRADE_F64_KOUTER2) return 0;
+    return n <= 16 * GRADE_CUS ? 1 : (n <= 32 * GRADE_CUS ? 2 : 0);
+}
+
+int grade_count_rows(const ActiveSet &as, int precision, int sched, int64_t n) {
+    const int sc = grade_sched_resolve(as, precision, sched, n), few = few_groups(n, sc);
+    return few ? 16 * few : (sc == GRADE_F64_PAIR ? GF2_ROWS : GRADE_ROWS);
 }
 
 void launch_grade(const ActiveSet &as, int precision, const double *brow, int ldb, int64_t ldn, int64_t n,
@@ -1502,7 +1629,7 @@ void launch_grade(const ActiveSet &as, int precision, const double *brow, int ld
     if (n == 0) return;
     MTP_CHECK(ldb >= (as.m + 31) / 32 * 32, MTP_E_INVAL, "grade: row length below the padded row length");
     MTP_CHECK(ldn >= n, MTP_E_INVAL, "grade: column stride below the row count");
-    sched = grade_sched_resolve(as, precision, sched);
+    sched = grade_sched_resolve(as, precision, sched, n);
     if (sched == GRADE_I8) {
         MTP_CHECK(as.KP8 == (as.m + 63) / 64 * 64 && as.s8.ptr, MTP_E_INVAL, "grade: digits of A^-1 not prepared");
         MTP_CHECK(ldb >= as.KP8, MTP_E_INVAL, "grade: rows not padded to a multiple of 64 columns");
@@ -1519,9 +1646,12 @@ void launch_grade(const ActiveSet &as, int precision, const double *brow, int ld
         MTP_CHECK(as.NK64 == (as.m + 31) / 32 && as.lane64.ptr, MTP_E_INVAL, "grade: A^-1 not staged");
         MTP_CHECK(ldb >= 32 * as.NK64, MTP_E_INVAL, "grade: rows not padded to a multiple of 32 columns");
         const bool big = sched == GRADE_F64_KOUTER;   // eight k steps per chunk, else two, two chunks ahead
+        const int few = few_groups(n, sched);
 #define MTP_KOUTER_CASE(K)                                                                  \
     case K:                                                                                 \
-        if (big)                                                                            \
+        if (few)                                                                            \
+            launch_grade_few<K>(few, as, brow, ldn, n, gamma, argmax, st, thr, sel_blk);    \
+        else if (big)                                                                         \
             launch_grade_f64_kouter<K, 8, 1>(as, brow, ldn, n, gamma, argmax, st, thr, sel_blk); \
         else                                                                                \
             launch_grade_f64_kouter<K, 2, 2>(as, brow, ldn, n, gamma, argmax, st, thr, sel_blk); \

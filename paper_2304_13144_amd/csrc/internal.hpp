@@ -150,7 +150,8 @@ constexpr int GRADE_ROWS = 64;
 // GRADE_F64_PAIR: as GRADE_F64_REG in blocks of 32 rows, two blocks per CU;
 // GRADE_F64_KOUTER: FP64 MFMA with k outermost, the rows streamed in chunks
 // of eight k steps (m <= 288; one block per CU); GRADE_F64_KOUTER2: the same
-// in chunks of two k steps (two blocks per CU)
+// in chunks of two k steps (two blocks per CU); both take blocks of 16 or 32
+// rows when there are too few rows for 64-row blocks on every CU
 enum {
     GRADE_AUTO = 0,
     GRADE_F64_REG = 1,
@@ -162,7 +163,7 @@ enum {
 };
 bool grade_sched_valid(const ActiveSet &as, int precision, int sched);
 // rows per preselection count the grade writes under a schedule (divides GRADE_ROWS)
-int grade_count_rows(const ActiveSet &as, int precision, int sched);
+int grade_count_rows(const ActiveSet &as, int precision, int sched, int64_t n);
 void launch_grade(const ActiveSet &as, int precision, const double *brow, int ldb, int64_t ldn, int64_t n,
                   double *gamma, int32_t *argmax, hipStream_t st, double thr = 0.0, int32_t *sel_blk = nullptr,
                   int sched = GRADE_AUTO);
