@@ -101,14 +101,15 @@ struct mtp_nbrs {
     mtp::DevBuf r;        // [N*maxn*3] FP64 r_ij
     mtp::DevBuf j;        // [N*maxn] int32
     mtp::DevBuf shift;    // [N*maxn] int32 packed (3 x int8, x in the low byte; top byte: opposite bin offset)
-    mtp::DevBuf pre;      // [N*n_types*64] uint16 list position where each bin offset's run starts
+    mtp::DevBuf runs;     // [N*n_types*32] uint32 per bin offset: the run's first list position, places present
+    mtp::DevBuf rank;     // [N] int32 place of the atom within its bin
     mtp::DevBuf rev;      // [N*maxn] int32 flat index of (j, i, -n)
     mtp::DevBuf tcnt;     // [N*n_types] int32 neighbors per species
     mtp::DevBuf atom_cfg; // [N] int32
     mtp::DevBuf cfg_geo;  // per cfg geometry (see neighbors.hip)
     mtp::DevBuf bin_count, bin_start, bin_cursor, bin_atoms, atom_bin, atom_wrap;
-    // atoms in bin order: position wrapped into the cell, packed -wrap, species
-    mtp::DevBuf stage_x, stage_w, stage_t;
+    // atoms in bin order: position wrapped into the cell, packed -wrap and species
+    mtp::DevBuf stage_x, stage_w;
     mtp::DevBuf flags;    // [4] int32: overflow, max count, overlap, spare
     int64_t bins_cap = 0;
 };

@@ -1,0 +1,104 @@
+"""Neighbor build at the edges of its cases: one launch for everything before
+the search (up to 2048 atoms in up to 64 configurations) or the general
+launches; bins that fit one window of candidates or not; more atoms in a bin
+than a run's mask holds (23); bin offsets past the run table (32, cells below
+the cut-off); atoms far outside an open cell (the float32 sieve rules nothing
+out).  Lists are compared with the oracle's, exactly, and between the two
+forms, entry by entry; a wrong reverse pair shows in the forces (FP64 bar
+1e-10 of the largest)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import mtp as om
+from oracle import neighbors as onb
+from paper_2304_13144_amd import api, synth
+
+pytestmark = pytest.mark.gpu
+R_CUT = 5.0
+
+
+def _lattice(a, reps, sigma, r):
+    pos, cell = synth.lattice("bcc", a, reps)
+    return pos + r.normal(0.0, sigma, pos.shape), cell
+
+
+def _case(name, n_types):
+    r = np.random.default_rng([len(name), n_types])
+    pbc = (True, True, True)
+    if name == "gas":            # oblique, uneven bins, some of them empty
+        cell = np.array([[22.0, 0.0, 0.0], [6.0, 21.0, 0.0], [-4.0, 5.0, 23.0]])
+        pos = r.random((330, 3)) @ cell + 40.0 * r.integers(-1, 2, (330, 1))
+    elif name == "drop":         # 54 atoms within 5 A, open: a bin's places pass 23
+        pos, _ = _lattice(1.7, (3, 3, 3), 0.05, r)
+        pos, cell, pbc = pos + 10.0, np.eye(3) * 24.0, (False, False, False)
+    elif name == "dense":        # more candidates than one window holds
+        pos, cell = _lattice(1.9, (6, 6, 6), 0.05, r)
+    elif name == "thin":         # 45 bin offsets
+        pos, cell = _lattice(2.3, (2, 6, 6), 0.1, r)
+    elif name == "tiny":         # 125 bin offsets or more
+        pos, cell = _lattice(2.7, (1, 1, 1), 0.1, r)
+    else:                        # "outside": two groups hundreds of cells away from an open cell
+        pos, cell = _lattice(3.3, (3, 3, 3), 0.1, r)
+        pos, pbc = np.concatenate([pos, pos[:20] + 900.0, pos[5:30] - 1500.0]), (False, True, False)
+        pos[:, 1] = np.where(np.abs(pos[:, 1]) > 800.0, pos[:, 1] % cell[1, 1], pos[:, 1])
+    return synth.Config(pos, r.integers(0, n_types, len(pos)).astype(np.int32), cell, pbc)
+
+
+def _rows(nbrs, batch):
+    count, j, shift = (x.cpu().numpy() for x in nbrs.export(batch))
+    return [(j[i, :count[i]], shift[i, :count[i]]) for i in range(len(count))]
+
+
+@pytest.mark.parametrize("n_types", [1, 2, 3, 4])
+@pytest.mark.parametrize("name", ["gas", "drop", "dense", "thin", "tiny", "outside"])
+def test_lists_and_reverse_pairs(name, n_types):
+    c = _case(name, n_types)
+    pot = om.Potential(8, n_types, 2.0, R_CUT)
+    theta = synth.theta_normal(1, n_types, pot.n_lin, pot.n_rad)
+    m = api.Model.create(8, n_types, 2.0, R_CUT)
+    m.set_params(theta)
+    pairs = onb.neighbors(c.pos, c.cell, c.pbc, R_CUT)
+    cap = int(np.bincount(pairs.i, minlength=len(c.pos)).max()) + 1
+    b = api.Batch([c])
+    nb = api.Neighbors().build(m, b, max_nbrs=cap)
+    rows = _rows(nb, b)
+    for i, (j, sh) in enumerate(rows):
+        mine = pairs.i == i
+        want = sorted((int(a), *map(int, s)) for a, s in zip(pairs.j[mine], pairs.shift[mine]))
+        assert sorted((int(a), *map(int, s)) for a, s in zip(j, sh)) == want, i
+        assert np.all(np.diff(c.types[j]) >= 0)
+    F = om.energy_forces_stress(pot, theta, c.pos, c.types, c.cell, pairs)[1]
+    out = api.energy_forces_stress(m, b, nb, "fp64")
+    assert np.abs(out["forces"].cpu().numpy() - F).max() <= 1e-10 * max(1.0, np.abs(F).max())
+    # the general launches: too many atoms, too many configurations
+    r = np.random.default_rng(5)
+    pos, cell = _lattice(3.3, (11, 11, 11), 0.1, r)
+    large = synth.Config(pos, r.integers(0, n_types, len(pos)).astype(np.int32), cell)
+    pos, cell = _lattice(3.3, (1, 1, 1), 0.1, r)
+    few = synth.Config(pos, np.zeros(2, np.int32), cell)
+    for cfgs, at in (([large, c], 1), ([few] * 40 + [c] + [few] * 40, 40)):
+        big = api.Batch(cfgs)
+        nbig = api.Neighbors().build(m, big, max_nbrs=max(cap, 70))
+        first = sum(len(x.pos) for x in cfgs[:at])
+        for i, (j, sh) in enumerate(_rows(nbig, big)[first:first + len(c.pos)]):
+            assert np.array_equal(j - first, rows[i][0]) and np.array_equal(sh, rows[i][1]), i
+        f = api.energy_forces_stress(m, big, nbig, "fp64")["forces"][first:first + len(c.pos)]
+        assert torch.equal(f, out["forces"])
+
+
+@pytest.mark.parametrize("n", [1, 2047, 2048, 2049])
+def test_either_side_of_the_one_launch_form(n):
+    r = np.random.default_rng(n)
+    pos, cell = _lattice(3.3, (11, 11, 11), 0.1, r)
+    keep = np.sort(r.permutation(len(pos))[:n])
+    c = synth.Config(pos[keep], np.zeros(n, np.int32), cell)
+    m = api.Model.create(8, 1, 2.0, R_CUT)
+    pairs = onb.neighbors(c.pos, c.cell, c.pbc, R_CUT)
+    b = api.Batch([c])
+    rows = _rows(api.Neighbors().build(m, b, max_nbrs=80), b)
+    counts = np.bincount(pairs.i, minlength=n)
+    assert [len(j) for j, _ in rows] == counts.tolist()
+    ends = np.cumsum(counts)
+    for i, (j, _) in enumerate(rows):
+        assert sorted(j.tolist()) == sorted(pairs.j[ends[i] - counts[i]:ends[i]].tolist())
