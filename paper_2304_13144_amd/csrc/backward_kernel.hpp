@@ -120,11 +120,11 @@ __device__ inline void tangent_moments_scattered(const BwdArgs &b, const AtomCtx
     const T x0 = T(-(a.r_min + a.r_cut) / (a.r_cut - a.r_min));
 #pragma unroll
     for (int k = 0; k < NCP; ++k) Md[k] = T(0);
-    int zj = 0, tend = c.tc[0];
+    const SpeciesEnds species(c);
     for (int p = sub; p < c.ntot; p += K) {
-        while (p >= tend && zj < nt - 1) tend += tcount(a, c, ++zj);
+        const int zj = species(p);
         const T x = T(c.rp[3 * p]), y = T(c.rp[3 * p + 1]), z = T(c.rp[3 * p + 2]);
-        const T r = sqrt(x * x + y * y + z * z);
+        const T r = sqrt(efs::norm2(x, y, z));
         if (!(r < rc)) continue;
         T d0, d1, d2;
         pair_dr<T>(b, c.atom, c.atom * (int64_t)a.max_nbrs + p, x, y, z, d0, d1, d2);
@@ -184,12 +184,14 @@ __global__ __launch_bounds__(512) void bwd_moments_contract(const BwdArgs b) {
     __shared__ T c_s[NR * MAX_TYPES * MAX_TYPES * NPOLY];
     __shared__ T sM[NCP][64], sD[NCP][64];
     __shared__ Dual<T> sum[Fact<L, K>::ROWS][64];
-    load_coefs<T, NR, 64 * K>(a, c_s);
     const int sub = threadIdx.x % K, la = threadIdx.x / K;
     const AtomCtx c = atom_ctx<K, 64 * K>(a);
+    const PairVector first(a, c, sub);
+    load_coefs<T, NR, 64 * K>(a, c_s);
+    __syncthreads();
     {
         T M[NCP];
-        moments_scattered<T, L, K>(a, c, c_s, M);
+        moments_scattered<T, L, K>(a, c, c_s, first, M);
 #pragma unroll
         for (int i = 0; i < NCP / K; ++i) sM[sub * (NCP / K) + i][la] = M[i];
     }
@@ -235,10 +237,21 @@ __global__ __launch_bounds__(256) void bwd_pairs(const BwdArgs b) {
     {
         const T *pv = static_cast<const T *>(a.dmbuf);
         const T *pt = static_cast<const T *>(b.dtbuf);
-        for (int k = sub; k < NC; k += K) {
-            s_dv[k][la] = c.live ? pv[(int64_t)k * a.n_atoms + c.slot] : T(0);
-            s_dt[k][la] = c.live ? pt[(int64_t)k * a.n_atoms + c.slot] : T(0);
+        // loaded unconditionally, in bounds, so that all loads are in flight together
+        constexpr int N = (NC + K - 1) / K;
+        T v[N], t[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int64_t at = (int64_t)(i * K + sub < NC ? i * K + sub : NC - 1) * a.n_atoms + (c.live ? c.slot : 0);
+            v[i] = pv[at];
+            t[i] = pt[at];
         }
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            if (i * K + sub < NC) {
+                s_dv[i * K + sub][la] = c.live ? v[i] : T(0);
+                s_dt[i * K + sub][la] = c.live ? t[i] : T(0);
+            }
     }
     __syncthreads();
     const T gE = (c.live && b.gE) ? T(b.gE[b.atom_cfg[c.atom]]) : T(0);
@@ -248,10 +261,10 @@ __global__ __launch_bounds__(256) void bwd_pairs(const BwdArgs b) {
         T acc[ND];
 #pragma unroll
         for (int k = 0; k < ND; ++k) acc[k] = T(0);
-        for (int qq = sub; qq < tcount(a, c, t); qq += K) {
+        for (int qq = sub; qq < tcount(c, t); qq += K) {
             const int p = gstart + qq;
             const T x = T(c.rp[3 * p]), y = T(c.rp[3 * p + 1]), z = T(c.rp[3 * p + 2]);
-            const T r = sqrt(x * x + y * y + z * z);
+            const T r = sqrt(efs::norm2(x, y, z));
             if (!(r < rc)) continue;
             T d0, d1, d2;
             pair_dr<T>(b, c.atom, c.atom * (int64_t)a.max_nbrs + p, x, y, z, d0, d1, d2);
@@ -310,7 +323,7 @@ __global__ __launch_bounds__(256) void bwd_pairs(const BwdArgs b) {
 #pragma unroll
             for (int i = 0; i < ND / K; ++i) cols[(int64_t)(t * ND + sub * (ND / K) + i) * a.ldn] = acc[i];
         }
-        gstart += tcount(a, c, t);
+        gstart += tcount(c, t);
     }
 }
 

@@ -58,6 +58,10 @@ template <typename T, int M, int K> __device__ inline void reduce_scatter(T (&v)
     rs_step<T, M, M, K / 2>(v, sub);
 }
 
+// x^2 + y^2 + z^2, its roundings spelled out: left to the compiler, which of
+// the products is rounded changes with the code around it
+template <typename T> __device__ inline T norm2(T x, T y, T z) { return fma(z, z, fma(x, x, y * y)); }
+
 // monomials x^a y^b z^c, a+b+c <= 3, in the order of monomial_index()
 template <typename T> __device__ inline void monomials(T x, T y, T z, T (&m)[20]) {
     m[0] = T(1); m[1] = x; m[2] = y; m[3] = z;
@@ -112,11 +116,42 @@ template <int K, int BS = 256> __device__ inline AtomCtx atom_ctx(const EfsArgs 
     return c;
 }
 
-// neighbors of species t, re-read from the (cached) counts: a runtime index
-// into c.tc would put the whole context in scratch memory
-template <typename A> __device__ inline int tcount(const A &a, const AtomCtx &c, int t) {
-    return c.live ? a.tcnt[c.atom * a.n_types + t] : 0;
+// neighbors of species t, picked by masks: a runtime index into c.tc would
+// put the whole context in scratch memory, and a read of the counts again is
+// a memory latency in the pair loop
+__device__ inline int tcount(const AtomCtx &c, int t) {
+    int n = 0;
+#pragma unroll
+    for (int k = 0; k < MAX_TYPES; ++k) n |= c.tc[k] & -(int)(t == k);
+    return n;
 }
+
+// Species of list position p (species come in order; p below the total)
+struct SpeciesEnds {
+    int e[MAX_TYPES - 1];
+    __device__ explicit SpeciesEnds(const AtomCtx &c) {
+        e[0] = c.tc[0];
+#pragma unroll
+        for (int k = 1; k < MAX_TYPES - 1; ++k) e[k] = e[k - 1] + c.tc[k];
+    }
+    __device__ int operator()(int p) const {
+        int z = 0;
+#pragma unroll
+        for (int k = 0; k < MAX_TYPES - 1; ++k) z += p >= e[k] ? 1 : 0;
+        return z;
+    }
+};
+
+// The pair vector of list position p of c, loaded in bounds whatever p is
+struct PairVector {
+    double x, y, z;
+    __device__ PairVector(const EfsArgs &a, const AtomCtx &c, int p) {
+        const double *r = c.rp + 3 * (p < a.max_nbrs ? p : a.max_nbrs - 1);
+        x = r[0];
+        y = r[1];
+        z = r[2];
+    }
+};
 
 // The radial coefficients c_{mu, z_i, z_j, beta} in LDS as
 // [mu][beta][z_i][z_j], the species padded to MAX_TYPES: the lanes of a
@@ -125,6 +160,7 @@ template <typename A> __device__ inline int tcount(const A &a, const AtomCtx &c,
 // [mu][z_i][z_j][beta] puts them NPOLY words apart), and beta steps by a
 // constant offset.
 constexpr int COEF_TT = MAX_TYPES * MAX_TYPES;
+// (The caller's barrier.)
 template <typename T, int NR, int BS = 256> __device__ inline void load_coefs(const EfsArgs &a, T *c_s) {
     const T *cg = coef_of<T>(a);
     const int nt = a.n_types, ntt = nt * nt;
@@ -133,7 +169,6 @@ template <typename T, int NR, int BS = 256> __device__ inline void load_coefs(co
         const int b = k % NPOLY, pair = (k / NPOLY) % ntt, mu = k / (NPOLY * ntt);
         c_s[(mu * NPOLY + b) * COEF_TT + (pair / nt) * MAX_TYPES + pair % nt] = cg[k];
     }
-    __syncthreads();
 }
 template <typename T> struct CoefRow {   // c_{mu, z_i, z_j, beta} over beta, from the LDS copy
     const T *p;
@@ -144,11 +179,16 @@ template <typename T> __device__ inline CoefRow<T> coef_row(const T *c_s, int mu
 }
 
 // ---- kernel 1: moments (eq. 3), LANES lanes per neighborhood -------------
+// Latency-bound in the small, so nothing in the pair loop waits for memory but
+// the next pair vector (the species of a position came from counts read again
+// at each change: FP32, 19,652 atoms, level 16, with the contraction 30.2 ->
+// 20.8 us).
 // Moments of the neighborhood of c, reduce-scattered over its K lanes: on
 // return M[i] of lane sub holds component sub NCP/K + i (NCP = NC padded to
-// a multiple of K).  c_s: the radial coefficients, already in LDS.
+// a multiple of K).  c_s: the radial coefficients, already in LDS; next: the
+// lane's first pair vector, loaded by the caller before its barrier.
 template <typename T, int L, int K>
-__device__ inline void moments_scattered(const EfsArgs &a, const AtomCtx &c, const T *c_s,
+__device__ inline void moments_scattered(const EfsArgs &a, const AtomCtx &c, const T *c_s, PairVector next,
                                          T (&M)[(Level<L>::NC + K - 1) / K * K]) {
     using LV = Level<L>;
     constexpr int NC = LV::NC, NR = LV::NRAD;
@@ -160,23 +200,12 @@ __device__ inline void moments_scattered(const EfsArgs &a, const AtomCtx &c, con
     constexpr int NCP = (NC + K - 1) / K * K;   // padded for the reduce-scatter
 #pragma unroll
     for (int k = 0; k < NCP; ++k) M[k] = T(0);
-    int zj = 0, tend = c.tc[0];
-    // the next pair vector is loaded while the current one is used
-    double nx = 0.0, ny = 0.0, nz = 0.0;
-    if (sub < c.ntot) {
-        nx = c.rp[3 * sub];
-        ny = c.rp[3 * sub + 1];
-        nz = c.rp[3 * sub + 2];
-    }
+    const SpeciesEnds species(c);
     for (int p = sub; p < c.ntot; p += K) {
-        while (p >= tend && zj < nt - 1) tend += tcount(a, c, ++zj);
-        const T x = T(nx), y = T(ny), z = T(nz);
-        if (p + K < c.ntot) {
-            nx = c.rp[3 * (p + K)];
-            ny = c.rp[3 * (p + K) + 1];
-            nz = c.rp[3 * (p + K) + 2];
-        }
-        const T r = sqrt(x * x + y * y + z * z);
+        const int zj = species(p);
+        const T x = T(next.x), y = T(next.y), z = T(next.z);
+        next = PairVector(a, c, p + K < c.ntot ? p + K : p);   // in flight while this one is used
+        const T r = sqrt(efs::norm2(x, y, z));
         if (!(r < rc)) continue;
         T fm[NR];
         {
@@ -209,11 +238,13 @@ __global__ __launch_bounds__(256) void efs_moments(const EfsArgs a) {
     constexpr int NC = LV::NC, NR = LV::NRAD;
     constexpr int NCP = (NC + K - 1) / K * K;
     __shared__ T c_s[NR * MAX_TYPES * MAX_TYPES * NPOLY];
-    load_coefs<T, NR>(a, c_s);
     const int sub = threadIdx.x % K;
     const AtomCtx c = atom_ctx<K>(a);
+    const PairVector first(a, c, sub);
+    load_coefs<T, NR>(a, c_s);
+    __syncthreads();
     T M[NCP];
-    moments_scattered<T, L, K>(a, c, c_s, M);
+    moments_scattered<T, L, K>(a, c, c_s, first, M);
     if (c.live) {
         T *out = static_cast<T *>(a.mbuf);
 #pragma unroll
@@ -584,12 +615,14 @@ __device__ __forceinline__ void moments_contract(const EfsArgs &a) {
     __shared__ T c_s[NR * MAX_TYPES * MAX_TYPES * NPOLY];
     __shared__ T sM[NCP][64];
     __shared__ T scratch[scratch_rows<T, L, K>()][64];
-    load_coefs<T, NR, 64 * K>(a, c_s);
     const int sub = threadIdx.x % K;
     const AtomCtx c = atom_ctx<K, 64 * K>(a);
+    const PairVector first(a, c, sub);
+    load_coefs<T, NR, 64 * K>(a, c_s);
+    __syncthreads();
     {
         T M[NCP];
-        moments_scattered<T, L, K>(a, c, c_s, M);
+        moments_scattered<T, L, K>(a, c, c_s, first, M);
         const int la = threadIdx.x / K;
 #pragma unroll
         for (int i = 0; i < NCP / K; ++i) sM[sub * (NCP / K) + i][la] = M[i];
@@ -629,12 +662,165 @@ __device__ inline void chebyshev(T u, T (&Tb)[NPOLY], T (&dT)[NPOLY]) {
 // they would cost 2 NC VGPRs per lane.  TD: the type dV/dM was computed in
 // (FP64 when the FP32 pair gradients of the mixed form follow an FP64
 // contraction that also fed the rows).
-template <typename T, int NC, int K, typename TD = T>
-__device__ inline void load_dm(const EfsArgs &a, const AtomCtx &c, int sub, T (&s_dm)[NC][256 / K]) {
-    const TD *din = static_cast<const TD *>(a.dmbuf);
-    const int la = threadIdx.x / K;
-    for (int k = sub; k < NC; k += K) s_dm[k][la] = c.live ? T(din[(int64_t)k * a.n_atoms + c.slot]) : T(0);
-    __syncthreads();
+// FP64: as the entries of the full symmetric tensors (component k over the
+// number of index orders that name it), the form mu_tensors works with.
+template <typename LV> constexpr int mu_first(int mu) {   // a mu's components are consecutive, by monomial index
+    int k = 0;
+    while (LV::comp_mu[k] != mu) ++k;
+    return k;
+}
+template <typename LV> constexpr int mu_count(int mu) {   // 1, 4, 10 or 20
+    int n = 0;
+    for (int k = 0; k < LV::NC; ++k) n += LV::comp_mu[k] == mu ? 1 : 0;
+    return n;
+}
+template <typename LV> constexpr int index_orders(int k) {
+    constexpr int by_mono[20] = {1, 1, 1, 1, 1, 2, 2, 1, 2, 1, 1, 3, 3, 3, 6, 3, 1, 3, 3, 1};
+    return by_mono[LV::comp_mono[k]];
+}
+// bit s: component k0 + s is named by `orders` orders (known at compile time, so that no table is read)
+template <typename LV, int K> constexpr unsigned orders_mask(int k0, int orders) {
+    unsigned m = 0;
+    for (int s = 0; s < K && k0 + s < LV::NC; ++s) m |= index_orders<LV>(k0 + s) == orders ? 1u << s : 0u;
+    return m;
+}
+// In two parts, so that the loads are in flight together and beside the
+// block's other first loads (one after the other, each behind a branch for
+// the last block's idle lanes, they took a memory latency each: 13 at level
+// 16 with four lanes).  The caller's barrier follows the second part.
+template <typename T, typename LV, int K> struct DmLoad {
+    static constexpr int N = (LV::NC + K - 1) / K;
+    T v[N];
+    template <typename TD> __device__ inline DmLoad(const EfsArgs &a, const AtomCtx &c, int sub, TD) {
+        const TD *din = static_cast<const TD *>(a.dmbuf) + (c.live ? c.slot : 0);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int k = i * K + sub;
+            v[i] = T(din[(int64_t)(k < LV::NC ? k : LV::NC - 1) * a.n_atoms]);
+        }
+    }
+    template <int I> __device__ inline void store_one(bool live, int sub, T (&s_dm)[LV::NC][256 / K]) const {
+        const int k = I * K + sub;
+        T x = live ? v[I] : T(0);
+        if constexpr (sizeof(T) == sizeof(double)) {
+            constexpr unsigned m2 = orders_mask<LV, K>(I * K, 2), m3 = orders_mask<LV, K>(I * K, 3),
+                               m6 = orders_mask<LV, K>(I * K, 6);
+            T w = T(1);
+            if (m2) w = (m2 >> sub) & 1 ? T(0.5) : w;
+            if (m3) w = (m3 >> sub) & 1 ? T(1.0 / 3.0) : w;
+            if (m6) w = (m6 >> sub) & 1 ? T(1.0 / 6.0) : w;
+            x *= w;
+        }
+        if (k < LV::NC) s_dm[k][threadIdx.x / K] = x;
+    }
+    template <int... I>
+    __device__ inline void store(bool live, int sub, T (&s_dm)[LV::NC][256 / K], std::integer_sequence<int, I...>) const {
+        (store_one<I>(live, sub, s_dm), ...);
+    }
+    __device__ inline void store(bool live, int sub, T (&s_dm)[LV::NC][256 / K]) const {
+        store(live, sub, s_dm, std::make_integer_sequence<int, N>{});
+    }
+};
+
+// FP64 pairs: P_mu(r) and its gradient from the symmetric tensors S of dE/dM
+// (LDS, [component][neighborhood la]).  With t_nu = S_nu . r^(nu - 1), a
+// vector, P = S_0 + sum_nu t_nu . r and grad P = sum_nu nu t_nu: 42 operations
+// for degrees 0 to 3 where monomials and their derivatives take 62, and the
+// ten cubic monomials are not held.  v: x y z; q: xx yy zz 2xy 2xz 2yz.
+template <typename LV, int MU, typename T, int W>
+__device__ __forceinline__ void mu_tensors(const T (&S)[LV::NC][W], int la, const T (&v)[3], const T (&q)[6], T &P,
+                                           T (&G)[3]) {
+    constexpr int K0 = mu_first<LV>(MU), N = mu_count<LV>(MU);
+    static_assert(N == 1 || N == 4 || N == 10 || N == 20, "a mu has the tensors of all degrees up to its largest");
+    const auto s = [&](int m) { return S[K0 + m][la]; };
+    P = s(0);
+    G[0] = G[1] = G[2] = T(0);
+    if constexpr (N > 1) {
+        T U[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) U[d] = G[d] = s(1 + d);
+        if constexpr (N > 4) {
+            const T t[3] = {fma(s(6), v[2], fma(s(5), v[1], s(4) * v[0])), fma(s(8), v[2], fma(s(7), v[1], s(5) * v[0])),
+                            fma(s(9), v[2], fma(s(8), v[1], s(6) * v[0]))};
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                U[d] += t[d];
+                G[d] = fma(T(2), t[d], G[d]);
+            }
+        }
+        if constexpr (N > 10) {
+            const T t[3] = {
+                fma(s(14), q[5], fma(s(12), q[4], fma(s(11), q[3], fma(s(15), q[2], fma(s(13), q[1], s(10) * q[0]))))),
+                fma(s(17), q[5], fma(s(14), q[4], fma(s(13), q[3], fma(s(18), q[2], fma(s(16), q[1], s(11) * q[0]))))),
+                fma(s(18), q[5], fma(s(15), q[4], fma(s(14), q[3], fma(s(19), q[2], fma(s(17), q[1], s(12) * q[0])))))};
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                U[d] += t[d];
+                G[d] = fma(T(3), t[d], G[d]);
+            }
+        }
+        P = fma(U[2], v[2], fma(U[1], v[1], fma(U[0], v[0], P)));
+    }
+}
+template <typename T> __device__ inline void quadratics(T x, T y, T z, T (&q)[6]) {
+    q[0] = x * x; q[1] = y * y; q[2] = z * z;
+    q[3] = (x + x) * y; q[4] = (x + x) * z; q[5] = (y + y) * z;
+}
+
+// r = sqrt(d2) and 1 / r from one reciprocal square root (Goldschmidt's
+// iteration, two residual corrections of r, one of 1/r): 11 operations for
+// the 27 of a square root and a division.  d2: a squared distance, neither 0
+// nor outside the range in which its square is a normal number.
+__device__ inline void root(double d2, double &r, double &rinv) {
+    const double y = __builtin_amdgcn_rsq(d2);
+    double g = d2 * y, h = 0.5 * y;
+    double e = fma(-h, g, 0.5);
+    h = fma(h, e, h);
+    g = fma(g, e, g);
+    g = fma(fma(-g, g, d2), h, g);
+    r = fma(fma(-g, g, d2), h, g);
+    h += h;
+    rinv = fma(fma(-r, h, 1.0), h, h);
+}
+
+// What an FP64 pair adds, mu by mu, so that one mu's P and gradient are live
+// at a time: to the force (f_mu grad P_mu), to its radial part (f_mu' P_mu)
+// and to the row's sums (ROWS; cut T_beta P_mu).
+template <typename LV, bool ROWS, int MU, typename T, int W, int ND>
+__device__ __forceinline__ void add_mu(const T (&S)[LV::NC][W], int la, const T (&v)[3], const T (&q)[6],
+                                       const T (&f)[LV::NRAD], const T (&fp)[LV::NRAD], const T (&Tb)[NPOLY], T cut,
+                                       T &radial, T (&g)[3], T (&dc)[ND]) {
+    T P, G[3];
+    mu_tensors<LV, MU>(S, la, v, q, P, G);
+    radial = fma(fp[MU], P, radial);
+    if constexpr (mu_count<LV>(MU) > 1)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) g[d] = fma(f[MU], G[d], g[d]);
+    if constexpr (ROWS) {
+        const T cP = cut * P;
+#pragma unroll
+        for (int b = 0; b < NPOLY; ++b) dc[MU * NPOLY + b] = fma(Tb[b], cP, dc[MU * NPOLY + b]);
+    }
+}
+template <typename LV, bool ROWS, typename T, int W, int ND, int... MU>
+__device__ __forceinline__ void add_all_mu(const T (&S)[LV::NC][W], int la, const T (&v)[3], const T (&q)[6],
+                                           const T (&f)[LV::NRAD], const T (&fp)[LV::NRAD], const T (&Tb)[NPOLY],
+                                           T cut, T &radial, T (&g)[3], T (&dc)[ND], std::integer_sequence<int, MU...>) {
+    (add_mu<LV, ROWS, MU>(S, la, v, q, f, fp, Tb, cut, radial, g, dc), ...);
+}
+// the row's sums alone
+template <typename LV, typename T, int W, int ND, int... MU>
+__device__ __forceinline__ void add_rows(const T (&S)[LV::NC][W], int la, const T (&v)[3], const T (&q)[6],
+                                         const T (&Tb)[NPOLY], T cut, T (&dc)[ND], std::integer_sequence<int, MU...>) {
+    const auto one = [&](auto mu) {
+        constexpr int M = decltype(mu)::value;
+        T P, G[3];
+        mu_tensors<LV, M>(S, la, v, q, P, G);
+        const T cP = cut * P;
+#pragma unroll
+        for (int b = 0; b < NPOLY; ++b) dc[M * NPOLY + b] = fma(Tb[b], cP, dc[M * NPOLY + b]);
+    };
+    (one(std::integral_constant<int, MU>{}), ...);
 }
 
 // ---- kernel 3: pair gradients and virial; LANES per atom ------------------
@@ -647,6 +833,14 @@ __device__ inline void load_dm(const EfsArgs &a, const AtomCtx &c, int sub, T (&
 // of the reverse pair (j, i) -- the gather then subtracts, for every atom,
 // the gradients its neighbors hold of it as one contiguous run of its own
 // slots, instead of following the reverse index pair by pair.
+//
+// What bounds it: at large n the scattered stores of the pair gradients (level
+// 8, 524,288 atoms with 58 neighbors: 395 us, 270 with the stores in list
+// order, 174 without them), else latencies at two or three wavefronts a SIMD
+// (the registers): hence everything a block needs first is loaded at once, and
+// one mu's tensors are in registers at a time.  256,000 atoms with 34
+// neighbors, level 16 with rows: 410 -> 373 us; 160 configurations at level
+// 24: 128 -> 97 us; 19,652 atoms FP32, level 16: 20.0 -> 19.0 us.
 //
 // R > 0 (FP64 only): the rest of the b row in the same pass (kernel 4's
 // work, Sec. II.C) -- R = 2 (FULL) the radial-coefficient part
@@ -662,13 +856,20 @@ __device__ inline void efs_forces_body(const EfsArgs &a, int64_t blk, T *c_s, T 
     constexpr int NC = LV::NC, NR = LV::NRAD, NL = LV::NLIN;
     constexpr int ND = NR * NPOLY;   // radial-coefficient sums per species (a multiple of K)
     static_assert(R == 0 || sizeof(T) == sizeof(double), "rows are FP64");
-    load_coefs<T, NR>(a, c_s);
     const int nt = a.n_types;
-    if constexpr (R == 2)   // before load_dm's barrier, which covers it
-        for (int k = threadIdx.x; k < NR * nt * nt * NPOLY; k += 256) s_col[k] = a.colmap[nt + NL + k];
     const int sub = threadIdx.x % K;
     const AtomCtx c = atom_ctx<K>(a, blk);
-    load_dm<T, NC, K, TD>(a, c, sub, s_dm);
+    PairVector next(a, c, sub);
+    const int32_t *rslot = G ? a.rev + c.atom * (int64_t)a.max_nbrs : nullptr;   // set only with gradients
+    int nrv = G ? rslot[sub < a.max_nbrs ? sub : a.max_nbrs - 1] : 0;
+    {
+        const DmLoad<T, LV, K> dm(a, c, sub, TD(0));
+        load_coefs<T, NR>(a, c_s);
+        if constexpr (R == 2)
+            for (int k = threadIdx.x; k < NR * nt * nt * NPOLY; k += 256) s_col[k] = a.colmap[nt + NL + k];
+        dm.store(c.live, sub, s_dm);
+        __syncthreads();
+    }
     double *brow = R > 0 && c.live ? a.brow + c.slot : nullptr;   // entry k at brow[k * ldn]
     const int64_t ldn = a.ldn;
     const int la = threadIdx.x / K;
@@ -680,49 +881,45 @@ __device__ inline void efs_forces_body(const EfsArgs &a, int64_t blk, T *c_s, T 
     for (int k = 0; k < 9; ++k) vir[k] = T(0);
     double fo[3] = {0.0, 0.0, 0.0};   // sum_j g_ij of this lane's pairs
     T *gout = static_cast<T *>(a.gbuf);
-    const int32_t *rslot = G ? a.rev + c.atom * (int64_t)a.max_nbrs : nullptr;   // set only with gradients
     int gstart = 0;
+    // The next pair vector is loaded while the current one is used (after a
+    // species' last pair the next species' first); the loads are unconditional
+    // (past the last pair it is read again, in bounds and unused), so that the
+    // wait for them leaves the gradient stores of the pair before in flight.
+    // The reverse slot of the next pair likewise (its store waits for it).
+    const auto in_list = [&](int p) { return p < a.max_nbrs ? p : a.max_nbrs - 1; };
     for (int t = 0; t < nt; ++t) {
-        const int tc = tcount(a, c, t);
+        const int tc = tcount(c, t);
         T dc[R == 2 ? ND : 1];
         if constexpr (R == 2)
 #pragma unroll
             for (int k = 0; k < ND; ++k) dc[k] = T(0);
-        // the next pair vector is loaded while the current one is used; the
-        // loads are unconditional (past the last pair the current one is read
-        // again, in bounds and unused), so that the wait for them leaves the
-        // gradient stores of the pair before in flight
-        const int p0 = gstart + sub < a.max_nbrs ? gstart + sub : a.max_nbrs - 1;
-        double nx = c.rp[3 * p0], ny = c.rp[3 * p0 + 1], nz = c.rp[3 * p0 + 2];
-        // the reverse slot of the next pair likewise (its store waits for it)
-        int nrv = G ? rslot[p0] : 0;
+        const int pnext = in_list(gstart + tc + sub);   // the next species' first pair
         // waited for here, once, so that the loop head does not wait for
         // every outstanding access (the stores included) on each pair
-        __asm__ volatile("" ::"v"(nx), "v"(ny), "v"(nz), "v"(nrv));
+        __asm__ volatile("" ::"v"(next.x), "v"(next.y), "v"(next.z), "v"(nrv));
         for (int q = sub; q < tc; q += K) {
             const int p = gstart + q;
-            const T x = T(nx), y = T(ny), z = T(nz);
+            const T x = T(next.x), y = T(next.y), z = T(next.z);
             const int rv = nrv;
-            const int pn = q + K < tc ? p + K : p;
-            nx = c.rp[3 * pn];
-            ny = c.rp[3 * pn + 1];
-            nz = c.rp[3 * pn + 2];
+            const int pn = q + K < tc ? p + K : (t + 1 < nt ? pnext : p);
+            next = PairVector(a, c, pn);
             if constexpr (G) nrv = rslot[pn];
-            const T r = sqrt(x * x + y * y + z * z);
+            constexpr bool F64 = sizeof(T) == sizeof(double);
+            const T d2 = efs::norm2(x, y, z);
+            T r, rinv;
+            if constexpr (F64) root(d2, r, rinv);
+            else r = sqrt(d2);
             T g0 = T(0), g1 = T(0), g2 = T(0);
             if (r < rc) {
-                T f[NR], fp[NR];
-                T qb[R == 2 ? NPOLY : 1];   // T_beta (R_cut - r)^2, for the row's c part
+                T f[NR], fp[NR], Tb[NPOLY];
+                const T d = rc - r;
+                const T cut = d * d;
                 {
                     const T u = fma(r, xs, x0);
-                    const T d = rc - r;
-                    const T cut = d * d;
                     const T dcut = T(-2) * d;
-                    T Tb[NPOLY], dT[NPOLY];
+                    T dT[NPOLY];
                     chebyshev<T, true>(u, Tb, dT);
-                    if constexpr (R == 2)
-#pragma unroll
-                        for (int b = 0; b < NPOLY; ++b) qb[b] = Tb[b] * cut;
 #pragma unroll
                     for (int mu = 0; mu < NR; ++mu) {
                         const CoefRow<T> cm = coef_row(c_s, mu, c.zi, t, nt);
@@ -736,36 +933,42 @@ __device__ inline void efs_forces_body(const EfsArgs &a, int64_t blk, T *c_s, T 
                         fp[mu] = fma(sp * xs, cut, s * dcut);
                     }
                 }
-                T mono[20];
-                efs::monomials(x, y, z, mono);
-                T P[NR], Gx[NR], Gy[NR], Gz[NR];
-#pragma unroll
-                for (int mu = 0; mu < NR; ++mu) P[mu] = Gx[mu] = Gy[mu] = Gz[mu] = T(0);
-#pragma unroll
-                for (int k = 0; k < NC; ++k) {
-                    const int mu = LV::comp_mu[k];
-                    const T dmk = s_dm[k][la];
-                    P[mu] = fma(dmk, mono[LV::comp_mono[k]], P[mu]);
-                    if (LV::comp_dmonox[k] >= 0)
-                        Gx[mu] = fma(dmk * T(LV::comp_dfacx[k]), mono[LV::comp_dmonox[k] < 0 ? 0 : LV::comp_dmonox[k]], Gx[mu]);
-                    if (LV::comp_dmonoy[k] >= 0)
-                        Gy[mu] = fma(dmk * T(LV::comp_dfacy[k]), mono[LV::comp_dmonoy[k] < 0 ? 0 : LV::comp_dmonoy[k]], Gy[mu]);
-                    if (LV::comp_dmonoz[k] >= 0)
-                        Gz[mu] = fma(dmk * T(LV::comp_dfacz[k]), mono[LV::comp_dmonoz[k] < 0 ? 0 : LV::comp_dmonoz[k]], Gz[mu]);
-                }
-                if constexpr (R == 2)
-#pragma unroll
-                    for (int b = 0; b < NPOLY; ++b)
-#pragma unroll
-                        for (int mu = 0; mu < NR; ++mu) dc[mu * NPOLY + b] = fma(qb[b], P[mu], dc[mu * NPOLY + b]);
-                const T rinv = T(1) / r;
                 T radial_part = T(0);
+                if constexpr (F64) {
+                    const T v[3] = {x, y, z};
+                    T q[6], g[3] = {T(0), T(0), T(0)};
+                    quadratics(x, y, z, q);
+                    add_all_mu<LV, R == 2>(s_dm, la, v, q, f, fp, Tb, cut, radial_part, g, dc,
+                                           std::make_integer_sequence<int, NR>{});
+                    g0 = g[0];
+                    g1 = g[1];
+                    g2 = g[2];
+                } else {
+                    T mono[20];
+                    efs::monomials(x, y, z, mono);
+                    T P[NR], Gx[NR], Gy[NR], Gz[NR];
 #pragma unroll
-                for (int mu = 0; mu < NR; ++mu) {
-                    radial_part = fma(fp[mu], P[mu], radial_part);
-                    g0 = fma(f[mu], Gx[mu], g0);
-                    g1 = fma(f[mu], Gy[mu], g1);
-                    g2 = fma(f[mu], Gz[mu], g2);
+                    for (int mu = 0; mu < NR; ++mu) P[mu] = Gx[mu] = Gy[mu] = Gz[mu] = T(0);
+#pragma unroll
+                    for (int k = 0; k < NC; ++k) {
+                        const int mu = LV::comp_mu[k];
+                        const T dmk = s_dm[k][la];
+                        P[mu] = fma(dmk, mono[LV::comp_mono[k]], P[mu]);
+                        if (LV::comp_dmonox[k] >= 0)
+                            Gx[mu] = fma(dmk * T(LV::comp_dfacx[k]), mono[LV::comp_dmonox[k] < 0 ? 0 : LV::comp_dmonox[k]], Gx[mu]);
+                        if (LV::comp_dmonoy[k] >= 0)
+                            Gy[mu] = fma(dmk * T(LV::comp_dfacy[k]), mono[LV::comp_dmonoy[k] < 0 ? 0 : LV::comp_dmonoy[k]], Gy[mu]);
+                        if (LV::comp_dmonoz[k] >= 0)
+                            Gz[mu] = fma(dmk * T(LV::comp_dfacz[k]), mono[LV::comp_dmonoz[k] < 0 ? 0 : LV::comp_dmonoz[k]], Gz[mu]);
+                    }
+                    rinv = T(1) / r;
+#pragma unroll
+                    for (int mu = 0; mu < NR; ++mu) {
+                        radial_part = fma(fp[mu], P[mu], radial_part);
+                        g0 = fma(f[mu], Gx[mu], g0);
+                        g1 = fma(f[mu], Gy[mu], g1);
+                        g2 = fma(f[mu], Gz[mu], g2);
+                    }
                 }
                 radial_part *= rinv;
                 g0 = fma(radial_part, x, g0);
@@ -786,15 +989,22 @@ __device__ inline void efs_forces_body(const EfsArgs &a, int64_t blk, T *c_s, T 
                 fo[2] += double(g2);
             }
         }
+        if (sub >= tc && t + 1 < nt) {   // no pair of this species on this lane: what it holds is not the next one's first
+            next = PairVector(a, c, pnext);
+            if constexpr (G) nrv = rslot[pnext];
+        }
         if constexpr (R == 2) {
+            int col[ND / K];
+#pragma unroll
+            for (int i = 0; i < ND / K; ++i) {
+                const int k = sub * (ND / K) + i, mu = k / NPOLY, b = k % NPOLY;
+                col[i] = s_col[((mu * nt + c.zi) * nt + t) * NPOLY + b];
+            }
             efs::reduce_scatter<T, ND, K>(dc, sub);
             if (brow) {
 #pragma unroll
-                for (int i = 0; i < ND / K; ++i) {
-                    const int k = sub * (ND / K) + i, mu = k / NPOLY, b = k % NPOLY;
-                    const int col = s_col[((mu * nt + c.zi) * nt + t) * NPOLY + b];
-                    if (col >= 0) brow[col * ldn] = dc[i];
-                }
+                for (int i = 0; i < ND / K; ++i)
+                    if (col[i] >= 0) brow[col[i] * ldn] = dc[i];
             }
         }
         gstart += tc;
@@ -837,12 +1047,15 @@ __device__ inline void efs_rows_body(const EfsArgs &a, int64_t blk, T (&s_dm)[Le
     const int sub = threadIdx.x % K;
     const AtomCtx c = atom_ctx<K>(a, blk);
     const bool full_rows = a.grade_mode == GRADE_FULL;
+    PairVector next(a, c, sub);
     if (full_rows) {
         // the kept columns of the c part, once per block in LDS: read from
         // global memory beside the row stores, each would wait for the store
         // before it (the two may alias)
+        const DmLoad<T, LV, K> dm(a, c, sub, T(0));
         for (int k = threadIdx.x; k < NR * nt * nt * NPOLY; k += 256) s_col[k] = a.colmap[nt + NL + k];
-        load_dm<T, NC, K>(a, c, sub, s_dm);   // (its barrier also covers s_col)
+        dm.store(c.live, sub, s_dm);
+        __syncthreads();
     }
     const int la = threadIdx.x / K;
     // entry k of this neighborhood's row: brow[k * ldn] (column-major rows)
@@ -858,41 +1071,24 @@ __device__ inline void efs_rows_body(const EfsArgs &a, int64_t blk, T (&s_dm)[Le
             T dc[ND];
 #pragma unroll
             for (int k = 0; k < ND; ++k) dc[k] = T(0);
-            const int tc = tcount(a, c, t);
-            double nx = 0.0, ny = 0.0, nz = 0.0;   // next pair vector, in flight
-            if (sub < tc) {
-                nx = c.rp[3 * (gstart + sub)];
-                ny = c.rp[3 * (gstart + sub) + 1];
-                nz = c.rp[3 * (gstart + sub) + 2];
-            }
+            const int tc = tcount(c, t);
+            if (t > 0 && (sub >= tcount(c, t - 1))) next = PairVector(a, c, gstart + sub);
             for (int q = sub; q < tc; q += K) {
                 const int p = gstart + q;
-                const T x = T(nx), y = T(ny), z = T(nz);
-                if (q + K < tc) {
-                    nx = c.rp[3 * (p + K)];
-                    ny = c.rp[3 * (p + K) + 1];
-                    nz = c.rp[3 * (p + K) + 2];
-                }
-                const T r = sqrt(x * x + y * y + z * z);
+                const T x = T(next.x), y = T(next.y), z = T(next.z);
+                next = PairVector(a, c, q + K < tc ? p + K : (t + 1 < nt ? gstart + tc + sub : p));
+                T r, rinv;
+                root(efs::norm2(x, y, z), r, rinv);
                 if (!(r < rc)) continue;
                 const T u = fma(r, xs, x0);
                 const T d = rc - r;
                 const T cut = d * d;
                 T Tb[NPOLY], dT[NPOLY];
                 chebyshev<T, false>(u, Tb, dT);
-                T mono[20];
-                efs::monomials(x, y, z, mono);
-                T P[NR];
-#pragma unroll
-                for (int mu = 0; mu < NR; ++mu) P[mu] = T(0);
-#pragma unroll
-                for (int k = 0; k < NC; ++k) P[LV::comp_mu[k]] = fma(s_dm[k][la], mono[LV::comp_mono[k]], P[LV::comp_mu[k]]);
-#pragma unroll
-                for (int b = 0; b < NPOLY; ++b) {
-                    const T qb = Tb[b] * cut;
-#pragma unroll
-                    for (int mu = 0; mu < NR; ++mu) dc[mu * NPOLY + b] = fma(qb, P[mu], dc[mu * NPOLY + b]);
-                }
+                const T v[3] = {x, y, z};
+                T qm[6];
+                quadratics(x, y, z, qm);
+                add_rows<LV>(s_dm, la, v, qm, Tb, cut, dc, std::make_integer_sequence<int, NR>{});
             }
             efs::reduce_scatter<T, ND, K>(dc, sub);
             if (brow) {
@@ -913,16 +1109,18 @@ __device__ inline void efs_rows_body(const EfsArgs &a, int64_t blk, T (&s_dm)[Le
 // TF: arithmetic of the pair gradients; TD: type of dE/dM, and of the rows
 // (rows exist only when TD is FP64: the FP64 form, or the mixed form whose
 // contraction ran in FP64 because the grade needs FP64 rows).
-template <typename TF, typename TD, int L, int K>
+// ROWS: with row blocks (a kernel of its own without: their registers would
+// cost the gradients wavefronts).
+template <typename TF, typename TD, int L, int K, bool ROWS>
 __global__ __launch_bounds__(256) void efs_forces_rows(const EfsArgs a, int64_t nblk) {
     using LV = Level<L>;
     constexpr int NCF = LV::NRAD * MAX_TYPES * MAX_TYPES * NPOLY;
     constexpr size_t FBYTES = sizeof(TF) * (NCF + LV::NC * (256 / K));
     constexpr size_t RBYTES = sizeof(double) * LV::NC * (256 / K) + sizeof(int32_t) * NCF;
-    constexpr bool ROWS = sizeof(TD) == sizeof(double);
+    static_assert(!ROWS || sizeof(TD) == sizeof(double), "rows are FP64");
     // one LDS area: a block takes either the gradient or the row part
-    __shared__ __attribute__((aligned(16))) char smem[FBYTES > RBYTES ? FBYTES : RBYTES];
-    if ((int64_t)blockIdx.x < nblk) {
+    __shared__ __attribute__((aligned(16))) char smem[ROWS && RBYTES > FBYTES ? RBYTES : FBYTES];
+    if (!ROWS || (int64_t)blockIdx.x < nblk) {
         TF *c_s = reinterpret_cast<TF *>(smem);
         auto &s_dm = *reinterpret_cast<TF (*)[LV::NC][256 / K]>(c_s + NCF);
         if (a.gbuf)
@@ -1034,8 +1232,15 @@ template <int L, typename TF, typename TD> int launch_fr_level_t(const EfsArgs &
                 return;                                                                                  \
             }                                                                                            \
         }                                                                                                \
-        hipLaunchKernelGGL((efs_forces_rows<TF, TD, LEVEL, K>), dim3(rows ? 2 * grid : grid), dim3(256),  \
-                           0, a.stream, a, (int64_t)grid);                                               \
+        if constexpr (sizeof(TD) == sizeof(double)) {                                                    \
+            if (rows) {                                                                                  \
+                hipLaunchKernelGGL((efs_forces_rows<TF, TD, LEVEL, K, true>), dim3(2 * grid), dim3(256),  \
+                                   0, a.stream, a, (int64_t)grid);                                       \
+                return;                                                                                  \
+            }                                                                                            \
+        }                                                                                                \
+        hipLaunchKernelGGL((efs_forces_rows<TF, TD, LEVEL, K, false>), dim3(grid), dim3(256), 0,          \
+                           a.stream, a, (int64_t)grid);                                                  \
     }                                                                                                    \
     template <typename TD> static int launch_fr_td##LEVEL(const EfsArgs &a) {                            \
         if (a.n_atoms == 0) return 0;                                                                    \
