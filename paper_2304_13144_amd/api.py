@@ -450,6 +450,7 @@ class MTPEnergy(torch.autograd.Function):
         model.set_params(theta.detach())
         out = energy_forces_stress(model, batch, nbrs, precision, site_energies=False)
         ctx.save_for_backward(theta.detach().clone())
+        ctx.theta_host = model.theta()   # the library's host copy: no wait for the GPU here or in the backward
         ctx.model, ctx.batch, ctx.nbrs, ctx.precision = model, batch, nbrs, precision
         ctx.generation = nbrs.generation
         return out["energy"], out["forces"], out["stress"]
@@ -459,9 +460,8 @@ class MTPEnergy(torch.autograd.Function):
         (theta,) = ctx.saved_tensors
         if ctx.nbrs.generation != ctx.generation:
             raise RuntimeError("MTPEnergy.backward: the neighbor lists were rebuilt after this forward")
-        th = theta.cpu().numpy()
-        if not np.array_equal(ctx.model.theta, th):
-            ctx.model.set_params(th)
+        if not np.array_equal(ctx.model.theta(), ctx.theta_host):
+            ctx.model.set_params(theta)
         g = efs_backward(ctx.model, ctx.batch, ctx.nbrs, gE, gF, gS, ctx.precision)
         return g, None, None, None, None
 

@@ -62,36 +62,39 @@ void choose_gauge(mtp_model *m) {
     const int blk = T * T * NPOLY;
     const int base = T + L;
     std::vector<int> drop;
+    std::vector<double> col, q;
+    std::vector<char> used;
     for (int mu = 0; mu < R; ++mu) {
         const int rows = mu + 1;
         // columns of the block as vectors of length rows
-        std::vector<std::vector<double>> col(blk, std::vector<double>(rows));
+        col.resize((size_t)blk * rows);
         for (int c = 0; c < blk; ++c)
-            for (int r = 0; r < rows; ++r) col[c][r] = m->theta_host[base + r * blk + c];
-        std::vector<bool> used(blk, false);
+            for (int r = 0; r < rows; ++r) col[(size_t)c * rows + r] = m->theta_host[base + r * blk + c];
+        used.assign(blk, 0);
+        q.resize(rows);
         for (int step = 0; step < rows; ++step) {
             int best = -1;
             double bn = -1.0;
             for (int c = 0; c < blk; ++c) {
                 if (used[c]) continue;
                 double nn = 0.0;
-                for (double v : col[c]) nn += v * v;
+                for (int r = 0; r < rows; ++r) nn += col[(size_t)c * rows + r] * col[(size_t)c * rows + r];
                 if (nn > bn) {
                     bn = nn;
                     best = c;
                 }
             }
-            used[best] = true;
+            used[best] = 1;
             drop.push_back(base + mu * blk + best);
             const double nrm = std::sqrt(bn);
             if (nrm == 0.0) continue;
-            std::vector<double> q(rows);
-            for (int r = 0; r < rows; ++r) q[r] = col[best][r] / nrm;
+            for (int r = 0; r < rows; ++r) q[r] = col[(size_t)best * rows + r] / nrm;
             for (int c = 0; c < blk; ++c) {
                 if (used[c]) continue;
                 double d = 0.0;
-                for (int r = 0; r < rows; ++r) d += q[r] * col[c][r];
-                for (int r = 0; r < rows; ++r) col[c][r] -= d * q[r];
+                double *x = &col[(size_t)c * rows];
+                for (int r = 0; r < rows; ++r) d += q[r] * x[r];
+                for (int r = 0; r < rows; ++r) x[r] -= d * q[r];
             }
         }
     }
@@ -109,15 +112,17 @@ void choose_gauge(mtp_model *m) {
     }
 }
 
+// theta in FP64 and FP32 and the kept-column map: one buffer, one copy
 void upload_params(mtp_model *m) {
     MTP_HIP(hipSetDevice(m->device));
-    m->theta64.ensure(sizeof(double) * m->n_theta);
-    m->theta32.ensure(sizeof(float) * m->n_theta);
-    std::vector<float> t32(m->theta_host.begin(), m->theta_host.end());
-    MTP_HIP(hipMemcpy(m->theta64.ptr, m->theta_host.data(), sizeof(double) * m->n_theta, hipMemcpyHostToDevice));
-    MTP_HIP(hipMemcpy(m->theta32.ptr, t32.data(), sizeof(float) * m->n_theta, hipMemcpyHostToDevice));
-    m->colmap.ensure(sizeof(int32_t) * m->n_theta);
-    MTP_HIP(hipMemcpy(m->colmap.ptr, m->colmap_host.data(), sizeof(int32_t) * m->n_theta, hipMemcpyHostToDevice));
+    const size_t n = m->n_theta, bytes = n * (sizeof(double) + sizeof(float) + sizeof(int32_t));
+    m->params.ensure(bytes);
+    std::vector<char> host(bytes);
+    std::memcpy(host.data(), m->theta_host.data(), sizeof(double) * n);
+    float *t32 = reinterpret_cast<float *>(host.data() + sizeof(double) * n);
+    for (size_t k = 0; k < n; ++k) t32[k] = (float)m->theta_host[k];
+    std::memcpy(t32 + n, m->colmap_host.data(), sizeof(int32_t) * n);
+    MTP_HIP(hipMemcpy(m->params.ptr, host.data(), bytes, hipMemcpyHostToDevice));
 }
 
 mtp_model *new_model(int level, int n_types, double r_min, double r_cut, int device) {
@@ -281,8 +286,8 @@ void evaluate(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb, int p
     a.type = s->type;
     a.r_min = m->r_min;
     a.r_cut = m->r_cut;
-    a.th64 = m->theta64.as<double>();
-    a.th32 = m->theta32.as<float>();
+    a.th64 = m->th64();
+    a.th32 = m->th32();
     a.n_lin = m->basis.n_lin();
     a.site_e = want_e ? site : nullptr;
     a.gbuf = gbuf;
@@ -293,7 +298,7 @@ void evaluate(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb, int p
     a.ldn = ldn_of(n);
     a.ldb = ldb;
     a.grade_mode = o.mode;
-    a.colmap = m->colmap.as<int32_t>();
+    a.colmap = m->colmap();
     a.m = mm;
     a.precision = prec;
     const int sched = lanes_for(m, n, prec);
@@ -823,14 +828,14 @@ int mtp_b_rows(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb, mtp_
     a.type = s->type;
     a.r_min = m->r_min;
     a.r_cut = m->r_cut;
-    a.th64 = m->theta64.as<double>();
-    a.th32 = m->theta32.as<float>();
+    a.th64 = m->th64();
+    a.th32 = m->th32();
     a.n_lin = m->basis.n_lin();
     a.brow = m->brow.as<double>();
     a.ldn = ldn_of(n_idx);
     a.ldb = ldb;
     a.grade_mode = g;
-    a.colmap = m->colmap.as<int32_t>();
+    a.colmap = m->colmap();
     a.m = mm;
     a.precision = MTP_FP64;
     a.lanes = 4;
@@ -1276,8 +1281,8 @@ int mtp_efs_backward(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb
     a.type = s->type;
     a.r_min = m->r_min;
     a.r_cut = m->r_cut;
-    a.th64 = m->theta64.as<double>();
-    a.th32 = m->theta32.as<float>();
+    a.th64 = m->th64();
+    a.th32 = m->th32();
     a.n_lin = m->basis.n_lin();
     a.precision = p;
     a.ldn = ldn_of(n);

@@ -74,7 +74,10 @@ struct mtp_model {
     std::vector<double> theta_host;
     std::vector<int> kept;          // FULL-mode kept columns
     std::vector<int> colmap_host;   // full column -> kept column or -1
-    mtp::DevBuf theta64, theta32, colmap;
+    mtp::DevBuf params;             // theta (FP64), theta rounded to FP32, kept-column map: n_theta each
+    const double *th64() const { return params.as<double>(); }
+    const float *th32() const { return reinterpret_cast<const float *>(th64() + n_theta); }
+    const int32_t *colmap() const { return reinterpret_cast<const int32_t *>(th32() + n_theta); }
     mtp::ActiveSet act[4];          // indexed by mtp_grade_mode: neighborhood and configuration modes
     // schedules: 16 x (lanes of the moments / contraction) + (lanes of the pair gradients)
     int force_lanes = 0;            // set while the tuner times a schedule
