@@ -30,10 +30,10 @@ HIP_FLAGS = ["-O3", f"--offload-arch={ARCH}", "-std=c++17", "-fPIC", "-Wno-unuse
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-I", CSRC, "-I", GEN]
 # units compiled with the machine scheduler's ILP strategy: the level-16 FP64
-# moments / contraction kernel runs one wavefront per SIMD and waits on LDS
-# results; scheduled for ILP it measured 21.4 -> 20.6 us per launch on the
-# 16,384-atom alloy, while the pair pass measured slower under it (29.3 -> 32.3
-# us) and keeps the default scheduler in a unit of its own
+# moments / contraction kernel runs two wavefronts per SIMD and waits on LDS
+# results; scheduled for ILP it measured 18.6 -> 18.1 us per launch on the
+# 16,384-atom alloy, while the pair pass measured slower under it (25.6 -> 28.2
+# us), as did the other levels' units (level 24 moments / contraction 225 -> 265)
 ILP_UNITS = ("efs_level16_f64_mc.hip",)
 ILP_FLAGS = ["-mllvm", "--amdgpu-sched-strategy=max-ilp"]
 HOST_SOURCES = ["api.cpp", "basis.cpp", "prof.cpp"]

@@ -183,7 +183,7 @@ __global__ __launch_bounds__(512) void bwd_moments_contract(const BwdArgs b) {
     const EfsArgs &a = b.e;
     __shared__ T c_s[NR * MAX_TYPES * MAX_TYPES * NPOLY];
     __shared__ T sM[NCP][64], sD[NCP][64];
-    __shared__ Dual<T> sum[Fact<L, K>::ROWS][64];
+    __shared__ Dual<T> sum[Fact<L, K>::template rows<Dual<T>>()][64];
     const int sub = threadIdx.x % K, la = threadIdx.x / K;
     const AtomCtx c = atom_ctx<K, 64 * K>(a);
     const PairVector first(a, c, sub);

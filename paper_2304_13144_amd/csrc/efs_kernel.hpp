@@ -309,6 +309,20 @@ template <typename T, int L> constexpr bool expanded_program() {
     return sizeof(T) == sizeof(float) && Level<L>::EXPANDED;
 }
 
+// xi_alpha into LDS for the factorised program: read there by a wavefront as
+// one word, in order with its other LDS reads; a scalar load is waited for
+// together with everything outstanding.  256,000 atoms at level 16: 223 -> 203
+// us for moments and contraction, level 24: 237 -> 226 (the expanded program
+// reads xi in runs and is faster from scalar loads: 20.4 us, 26.6 from LDS, at
+// 19,652 atoms).  (The caller's barrier.)
+template <typename T, int L> constexpr int xi_words() { return expanded_program<T, L>() ? 1 : Level<L>::NLIN; }
+template <typename T, int L, int BS> __device__ inline void load_xi(const EfsArgs &a, T *s_xi) {
+    if constexpr (!expanded_program<T, L>()) {
+        const T *xi = xi_of<T>(a);
+        for (int k = threadIdx.x; k < Level<L>::NLIN; k += BS) s_xi[k] = xi[k];
+    }
+}
+
 // The clusters of the factorised program for NW wavefronts.
 template <int L, int NW> struct Fact {
     using LV = Level<L>;
@@ -334,6 +348,63 @@ template <int L, int NW> struct Fact {
         for (int i = 0; i < LV::NLOWC; ++i)
             if (LV::low_comp[i] == k) return true;
         return false;
+    }
+    // first of cluster P's sums where every cluster has rows of its own
+    static constexpr int base(int P) {
+        int n = 0;
+        for (int Q = 0; Q < P; ++Q) n += ncomp(Q);
+        return n;
+    }
+    // Every cluster's sums side by side in LDS, one barrier, each total added
+    // by the wavefront that needs it: where that leaves the block its room on
+    // the compute unit (beside the moments; eight wavefronts fill one by their
+    // registers, of four wavefronts two blocks do).  Otherwise one row per
+    // sum, and NW steps with a barrier each: 864 atoms at level 16 16.2 us,
+    // side by side 13.0; 16 configurations at level 12 10.6 and 9.2.
+    template <typename T> static constexpr bool side_by_side() {
+        return (base(NW) + LV::NC) * 64 * sizeof(T) <= (NW == 8 ? 112 : 64) * 1024;
+    }
+    template <typename T> static constexpr int rows() { return side_by_side<T>() ? (base(NW) > 0 ? base(NW) : 1) : ROWS; }
+    template <int P, typename T, int... I>
+    static __device__ __forceinline__ void put(const T (&d)[MAXC], T (*sum)[64], int lane,
+                                               std::integer_sequence<int, I...>) {
+        ((sum[base(P) + I][lane] = d[I]), ...);
+    }
+    // the total of sum k, clusters in order
+    template <int k, int P, typename T> static __device__ __forceinline__ void take(T (*sum)[64], int lane, T &v) {
+        constexpr int i = find(P, k);
+        if constexpr (i >= 0) {
+            constexpr bool first = [] {
+                for (int Q = 0; Q < P; ++Q)
+                    if (find(Q, k) >= 0) return false;
+                return true;
+            }();
+            const T x = sum[base(P) + i][lane];
+            v = first ? x : v + x;
+        }
+    }
+    template <int k, typename T, int... P>
+    static __device__ __forceinline__ T total(T (*sum)[64], int lane, std::integer_sequence<int, P...>) {
+        T v = T(0);
+        (take<k, P>(sum, lane, v), ...);
+        return v;
+    }
+    template <int k, typename T> static __device__ __forceinline__ T total(T (*sum)[64], int lane) {
+        return total<k, T>(sum, lane, std::make_integer_sequence<int, NW>{});
+    }
+    // wavefront P's components of dV/dM (all but the low ones, dealt out in turn)
+    template <int P, int k, typename T, typename OUT>
+    static __device__ __forceinline__ void out_one(T (*sum)[64], int lane, const OUT &out) {
+        if constexpr (k % (NW - 1) == P && !is_low(k)) out(k, total<k>(sum, lane));
+    }
+    template <int P, typename T, typename OUT, int... K>
+    static __device__ __forceinline__ void out_all(T (*sum)[64], int lane, const OUT &out,
+                                                   std::integer_sequence<int, K...>) {
+        (out_one<P, K>(sum, lane, out), ...);
+    }
+    template <typename T, int... Q>
+    static __device__ __forceinline__ void take_products(T (*sum)[64], int lane, T *X, std::integer_sequence<int, Q...>) {
+        ((X[Q] = total<LV::NC + Q>(sum, lane)), ...);
     }
     // Everything below is unrolled by index sequences, not loops: d must be
     // addressed by constants from the start to stay in registers.
@@ -361,7 +432,8 @@ template <int L, int NW> struct Fact {
     template <typename T, typename OUT, int... I>
     static __device__ __forceinline__ void low_out(const T *d, T (*sum)[64], int lane, const OUT &out,
                                                    std::integer_sequence<int, I...>) {
-        (out(LV::low_comp[I], sum[LV::low_comp[I]][lane] + d[I]), ...);
+        if constexpr (side_by_side<T>()) (out(LV::low_comp[I], total<LV::low_comp[I]>(sum, lane) + d[I]), ...);
+        else (out(LV::low_comp[I], sum[LV::low_comp[I]][lane] + d[I]), ...);
     }
 };
 
@@ -399,15 +471,17 @@ template <int L, int NW> struct Fact {
 // The factorised contraction of one block's 64 neighborhoods: wavefront w
 // runs cluster w forward and back on the moments M, the last one the low
 // graphs besides; the shares of dV/dM and of the sums X_p are added in LDS
-// (sum), every wavefront on a slice of its own per step; then the last
-// wavefront closes the low graphs with the X_p while the others write dV/dM.
+// (sum): side by side and then each total, or every wavefront on a slice of
+// its own per step; then the last wavefront closes the low graphs with the X_p
+// while the others write dV/dM.
 // out(k, v): component k of dV/dM; site(V): the site energy (last wavefront).
 // No graph value passes between wavefronts and the trie walk is not repeated
-// by each, as in the expanded form.  Bound by FP64 issue at two wavefronts per
-// SIMD (256 VGPRs hold a cluster's sums and intermediates).  Level 24, 160
-// configurations, 76,930 atoms (energies, forces, stress): 1,539 us with the
-// expanded program in 25 launches through memory, 396 us in this one launch;
-// level 16, 16,384 atoms with rows: 27.8 -> 22.3 us for this launch.
+// by each, as in the expanded form.  Bound by latencies at two wavefronts per
+// SIMD (256 VGPRs hold a cluster's sums and intermediates; the FP64 units are
+// busy a quarter to two fifths of the time).  Level 24, 160 configurations,
+// 76,930 atoms (energies, forces, stress): 1,539 us with the expanded program
+// in 25 launches through memory, 225 us in this one launch; level 16, 16,384
+// atoms with rows: 27.8 -> 18.1 us for this launch.
 template <typename T, int L, bool WB, int NW, typename MP, typename XP, typename BP, typename OUT, typename SITE>
 __device__ __forceinline__ void fact_body(const MP &M, const XP &xi, const BP &sink, T (*sum)[64], const OUT &out,
                                           const SITE &site) {
@@ -422,25 +496,36 @@ __device__ __forceinline__ void fact_body(const MP &M, const XP &xi, const BP &s
         T d[FA::MAXC];
         MTP_BY_WAVE(FA::template cluster<P, WB>(M, p, xi, sink, d))
         if (wave == NW - 1) LV::template low_functions<WB>(gl, xi, sink, dz, V);
-        MTP_REDUCE_STEP(0)
-        MTP_REDUCE_STEP(1)
-        MTP_REDUCE_STEP(2)
-        MTP_REDUCE_STEP(3)
-        MTP_REDUCE_STEP(4)
-        MTP_REDUCE_STEP(5)
-        MTP_REDUCE_STEP(6)
-        MTP_REDUCE_STEP(7)
+        if constexpr (FA::template side_by_side<T>()) {
+            MTP_BY_WAVE(FA::template put<P>(d, sum, lane, std::make_integer_sequence<int, FA::ncomp(P)>{}))
+            __syncthreads();
+        } else {
+            MTP_REDUCE_STEP(0)
+            MTP_REDUCE_STEP(1)
+            MTP_REDUCE_STEP(2)
+            MTP_REDUCE_STEP(3)
+            MTP_REDUCE_STEP(4)
+            MTP_REDUCE_STEP(5)
+            MTP_REDUCE_STEP(6)
+            MTP_REDUCE_STEP(7)
+        }
     }
     if (wave == NW - 1) {
         T X[LV::NPROD], d[NCA];
+        if constexpr (FA::template side_by_side<T>()) {
+            FA::take_products(sum, lane, X, std::make_integer_sequence<int, LV::NPROD>{});
+        } else {
 #pragma unroll
-        for (int q = 0; q < LV::NPROD; ++q) X[q] = sum[LV::NC + q][lane];
+            for (int q = 0; q < LV::NPROD; ++q) X[q] = sum[LV::NC + q][lane];
+        }
         LV::template low_coupling<T>(gl, p, X, dz, V);
         if constexpr (LV::NLOW > 0) {
             LV::template low_reverse<T>(M, dz, d);
             FA::low_out(d, sum, lane, out, std::make_integer_sequence<int, LV::NLOWC>{});
         }
         site(V);
+    } else if constexpr (FA::template side_by_side<T>()) {
+        MTP_BY_WAVE(FA::template out_all<P>(sum, lane, out, std::make_integer_sequence<int, LV::NC>{}))
     } else {
         for (int k = wave; k < LV::NC; k += NW - 1)
             if (!FA::is_low(k)) out(k, sum[k][lane]);
@@ -558,13 +643,14 @@ __device__ inline void expanded_body(const EfsArgs &a, int64_t blk, const MA &M,
 // rows of LDS scratch the contraction needs besides the moments
 template <typename T, int L, int NW> constexpr int scratch_rows() {
     if constexpr (expanded_program<T, L>()) return Level<L>::NGRAPH;
-    else return Fact<L, NW>::ROWS;
+    else return Fact<L, NW>::template rows<T>();
 }
 
 // The contraction of the 64 neighborhoods of block blk, the moments read
 // through M.  sM: the moments' LDS, or NULL when they are in memory.
 template <typename T, int L, bool WB, int NW, typename MA>
-__device__ __forceinline__ void contract_body(const EfsArgs &a, int64_t blk, const MA &M, T (*scratch)[64], T (*sM)[64]) {
+__device__ __forceinline__ void contract_body(const EfsArgs &a, int64_t blk, const MA &M, const T *s_xi, T (*scratch)[64],
+                                              T (*sM)[64]) {
     static_assert(!WB || sizeof(T) == sizeof(double), "rows are FP64");
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t slot = blk * 64 + lane;
@@ -578,7 +664,7 @@ __device__ __forceinline__ void contract_body(const EfsArgs &a, int64_t blk, con
             if (live) dout[(int64_t)k * a.n_atoms] = v;
         };
         const auto site = [&](T V) { write_site<T>(a, slot, V); };
-        const XiPtr<T> xi{xi_of<T>(a)};
+        const XiPtr<T> xi{s_xi};
         if constexpr (WB)
             fact_body<T, L, true, NW>(M, xi, ColSink{a.brow, a.ldn, a.n_types, (uint32_t)slot}, scratch, out, site);
         else
@@ -598,9 +684,12 @@ __global__ __launch_bounds__(64 * contract_waves<L>()) void efs_contract(const E
     constexpr int NW = contract_waves<L>();
     __shared__ T scratch[scratch_rows<T, L, NW>()][64];
     __shared__ T sdm[expanded_program<T, L>() ? LV::NC : 1][64];
+    __shared__ T s_xi[xi_words<T, L>()];
+    load_xi<T, L, 64 * NW>(a, s_xi);
+    __syncthreads();
     const int64_t slot = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
     const int64_t sl = slot < a.n_atoms ? slot : 0;
-    contract_body<T, L, WB, NW>(a, blockIdx.x, ColLoad<T>{static_cast<const T *>(a.mbuf) + sl, a.n_atoms}, scratch, sdm);
+    contract_body<T, L, WB, NW>(a, blockIdx.x, ColLoad<T>{static_cast<const T *>(a.mbuf) + sl, a.n_atoms}, s_xi, scratch, sdm);
 }
 
 // Kernels 1 and 2 in one launch, K = NW = four or eight lanes per
@@ -615,10 +704,12 @@ __device__ __forceinline__ void moments_contract(const EfsArgs &a) {
     __shared__ T c_s[NR * MAX_TYPES * MAX_TYPES * NPOLY];
     __shared__ T sM[NCP][64];
     __shared__ T scratch[scratch_rows<T, L, K>()][64];
+    __shared__ T s_xi[xi_words<T, L>()];
     const int sub = threadIdx.x % K;
     const AtomCtx c = atom_ctx<K, 64 * K>(a);
     const PairVector first(a, c, sub);
     load_coefs<T, NR, 64 * K>(a, c_s);
+    load_xi<T, L, 64 * K>(a, s_xi);
     __syncthreads();
     {
         T M[NCP];
@@ -628,7 +719,7 @@ __device__ __forceinline__ void moments_contract(const EfsArgs &a) {
         for (int i = 0; i < NCP / K; ++i) sM[sub * (NCP / K) + i][la] = M[i];
     }
     __syncthreads();
-    contract_body<T, L, WB, K>(a, blockIdx.x, LdsCol<T>{&sM[0][threadIdx.x & 63]}, scratch, sM);
+    contract_body<T, L, WB, K>(a, blockIdx.x, LdsCol<T>{&sM[0][threadIdx.x & 63]}, s_xi, scratch, sM);
 }
 
 template <typename T, int L, bool WB>
