@@ -930,11 +930,10 @@ int mtp_md_run(const mtp_model *m, const mtp_system *s, mtp_nbrs *nb, int32_t ma
     m->md_f.ensure(sizeof(double) * 3 * (size_t)std::max<int64_t>(1, n));
     m->md_g.ensure(sizeof(double) * (size_t)std::max<int64_t>(1, n));
     m->md_invm.ensure(sizeof(double) * m->n_types);
-    m->md_scal.ensure(64);
     std::vector<double> invm(m->n_types);
     for (int t = 0; t < m->n_types; ++t) invm[t] = 1.0 / masses[t];
     MTP_HIP(hipMemcpyAsync(m->md_invm.ptr, invm.data(), sizeof(double) * invm.size(), hipMemcpyHostToDevice, st));
-    double *F = m->md_f.as<double>(), *gam = m->md_g.as<double>(), *gmax = m->md_scal.as<double>();
+    double *F = m->md_f.as<double>(), *gam = m->md_g.as<double>();
     const double h = 0.5 * dt * EV_A_AMU;
     // one step's grading: neighbor lists, forces and grades, gamma(cfg) = max_i gamma_i
     auto grade = [&]() -> double {
@@ -944,14 +943,12 @@ int mtp_md_run(const mtp_model *m, const mtp_system *s, mtp_nbrs *nb, int32_t ma
         o.gamma = gam;
         o.mode = g;
         evaluate(m, s, nb, p, o, st);
-        launch_argmax(gam, n, gmax, nullptr, st);
-        int32_t f[4];
-        double gm = 0.0;
-        MTP_HIP(hipMemcpyAsync(f, nb->flags.ptr, sizeof(f), hipMemcpyDeviceToHost, st));
-        MTP_HIP(hipMemcpyAsync(&gm, gmax, sizeof(double), hipMemcpyDeviceToHost, st));
+        launch_argmax(gam, n, nb->flags.as<StepRead>()->scal, nullptr, st);
+        StepRead rd{};
+        MTP_HIP(hipMemcpyAsync(&rd, nb->flags.ptr, sizeof(rd), hipMemcpyDeviceToHost, st));
         MTP_HIP(hipStreamSynchronize(st));
-        throw_nbr_flags(f, max_nbrs);
-        return gm;
+        throw_nbr_flags(rd.flags, max_nbrs);
+        return rd.scal[0];
     };
     *n_saved = 0;
     *steps_done = 0;
@@ -966,9 +963,10 @@ int mtp_md_run(const mtp_model *m, const mtp_system *s, mtp_nbrs *nb, int32_t ma
     };
     if (n == 0 || !record(0, grade())) return MTP_OK;
     for (int step = 1; step <= n_steps; ++step) {
-        launch_md_step(0, n, pos, vel, F, s->type, m->md_invm.as<double>(), h, dt, st);
+        // (from the second step on with the last half kick of the step before)
+        launch_md_kick_drift(step > 1 ? 2 : 1, n, pos, vel, F, s->type, m->md_invm.as<double>(), h, dt, st);
         if (!record(step, grade())) break;
-        launch_md_step(1, n, pos, vel, F, s->type, m->md_invm.as<double>(), h, dt, st);
+        if (step == n_steps) launch_md_kick(n, vel, F, s->type, m->md_invm.as<double>(), h, st);
         *steps_done = step;
     }
     MTP_HIP(hipStreamSynchronize(st));
@@ -996,12 +994,10 @@ int mtp_relax_fire(const mtp_model *m, const mtp_system *s, mtp_nbrs *nb, int32_
     m->md_v.ensure(sizeof(double) * 3 * (size_t)std::max<int64_t>(1, n));
     m->md_g.ensure(sizeof(double) * (size_t)std::max<int64_t>(1, n));
     m->md_invm.ensure(sizeof(double) * m->n_types);
-    m->md_scal.ensure(64);
     std::vector<double> invm(m->n_types);
     for (int t = 0; t < m->n_types; ++t) invm[t] = 1.0 / masses[t];
     MTP_HIP(hipMemcpyAsync(m->md_invm.ptr, invm.data(), sizeof(double) * invm.size(), hipMemcpyHostToDevice, st));
     double *F = m->md_f.as<double>(), *v = m->md_v.as<double>(), *gam = m->md_g.as<double>();
-    double *scal = m->md_scal.as<double>();   // [0] gamma max, [1..4] FIRE norms
     launch_zero(v, sizeof(double) * 3 * (size_t)std::max<int64_t>(1, n), st);
     double nrm[4] = {0, 0, 0, 0};
     // grading of a configuration: neighbor lists, forces and grades, then
@@ -1013,16 +1009,15 @@ int mtp_relax_fire(const mtp_model *m, const mtp_system *s, mtp_nbrs *nb, int32_
         o.gamma = gam;
         o.mode = g;
         evaluate(m, s, nb, p, o, st);
+        double *scal = nb->flags.as<StepRead>()->scal;   // [0] gamma max, [1..4] FIRE norms
         launch_argmax(gam, n, scal, nullptr, st);
         launch_fire_norms(n, F, v, scal + 1, st);
-        int32_t f[4];
-        double h[5];
-        MTP_HIP(hipMemcpyAsync(f, nb->flags.ptr, sizeof(f), hipMemcpyDeviceToHost, st));
-        MTP_HIP(hipMemcpyAsync(h, scal, sizeof(h), hipMemcpyDeviceToHost, st));
+        StepRead rd{};
+        MTP_HIP(hipMemcpyAsync(&rd, nb->flags.ptr, sizeof(rd), hipMemcpyDeviceToHost, st));
         MTP_HIP(hipStreamSynchronize(st));
-        throw_nbr_flags(f, max_nbrs);
-        for (int k = 0; k < 4; ++k) nrm[k] = h[1 + k];
-        return h[0];
+        throw_nbr_flags(rd.flags, max_nbrs);
+        for (int k = 0; k < 4; ++k) nrm[k] = rd.scal[1 + k];
+        return rd.scal[0];
     };
     *n_saved = 0;
     *steps_done = 0;
@@ -1062,7 +1057,7 @@ int mtp_relax_fire(const mtp_model *m, const mtp_system *s, mtp_nbrs *nb, int32_
             alpha = 0.1;
             n_pos = 0;
         }
-        launch_md_step(0, n, pos, v, F, s->type, m->md_invm.as<double>(), dt * EV_A_AMU, dt, st);
+        launch_md_kick_drift(1, n, pos, v, F, s->type, m->md_invm.as<double>(), dt * EV_A_AMU, dt, st);
         if (!record(step, grade())) {
             stopped = true;
             break;

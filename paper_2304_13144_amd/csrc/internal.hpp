@@ -46,6 +46,13 @@ struct DevBuf {
 void launch_zero(void *p, size_t bytes, hipStream_t st);
 
 
+// what the MD and relaxation drivers read back per step, in one copy: the
+// build's status words and the step's scalars (gamma maximum, FIRE norms)
+struct StepRead {
+    int32_t flags[8];
+    double scal[5];
+};
+
 struct ActiveSet {
     int m = 0;
     bool valid = false;
@@ -88,7 +95,7 @@ struct mtp_model {
     mutable mtp::DevBuf gbuf, virial, sitebuf, brow, gamma_ws, argmax_ws, work, sums, mbuf, dmbuf, dtbuf, rows;
     mutable mtp::DevBuf selblk;     // per-block preselection counts written by the grade kernels
     mutable mtp::DevBuf cfgrows, cfgpart;   // configuration-mode rows and their chunk partials
-    mutable mtp::DevBuf md_f, md_g, md_invm, md_scal;   // MD driver: forces, grades, 1/mass, {gamma max, norms}
+    mutable mtp::DevBuf md_f, md_g, md_invm;   // MD driver: forces, grades, 1/mass
     mutable mtp::DevBuf md_v;                           // relaxation: FIRE velocities
     mutable mtp::DevBuf fit_y, fit_g, fit_part, fit_th;  // fitting: E/F/S, dL/d(E/F/S), loss partials, dL/dtheta
     // the configuration modes use the rows of their neighborhood mode (mode & 1)
@@ -113,7 +120,9 @@ struct mtp_nbrs {
     mtp::DevBuf bin_count, bin_start, bin_cursor, bin_atoms, atom_bin, atom_wrap;
     // atoms in bin order: position wrapped into the cell, packed -wrap and species
     mtp::DevBuf stage_x, stage_w;
-    mtp::DevBuf flags;    // [4] int32: overflow, max count, overlap, spare
+    // int32 [8] status words (overflow, largest count, overlap, faults, bins, wide bins, slots taken), then
+    // double [5] for a driver's scalars of the same step, read back with them
+    mtp::DevBuf flags;
     int64_t bins_cap = 0;
 };
 
@@ -205,13 +214,15 @@ void run_maxvol(ActiveSet &as, double *cand, int64_t n_cand, double thr, int max
 // column-major rows (entry (i, k) at src[k * ldn + i]) -> row-major dst [n][m]
 void launch_copy_rows(const double *src, int64_t ldn, int m, int64_t n, double *dst, hipStream_t st);
 // extrapolation-controlled runs: largest value and its lowest index (one
-// block; either output may be NULL); velocity-Verlet half steps (half 0:
-// kick and drift, 1: kick); the spherical fragment around the largest
+// block; either output may be NULL); velocity-Verlet half steps (kicks = 2:
+// with the half kick that ends the step before); the spherical fragment around the largest
 // grade: argmax, candidate keys over atoms x image shifts, ordered
 // compaction, gather.  H: host cell (rows = lattice vectors), per: host pbc.
 void launch_argmax(const double *g, int64_t n, double *best, int32_t *where, hipStream_t st);
-void launch_md_step(int half, int64_t n, double *x, double *v, const double *F, const int32_t *type,
-                    const double *inv_m, double h, double dt, hipStream_t st);
+void launch_md_kick_drift(int kicks, int64_t n, double *x, double *v, const double *F, const int32_t *type,
+                          const double *inv_m, double h, double dt, hipStream_t st);
+void launch_md_kick(int64_t n, double *v, const double *F, const int32_t *type, const double *inv_m, double h,
+                    hipStream_t st);
 // FIRE: out [4] = {F.v, F.F, v.v, max_i |F_i|^2}; v <- a v + b F
 void launch_fire_norms(int64_t n, const double *F, const double *v, double *out, hipStream_t st);
 void launch_fire_mix(int64_t n, double *v, const double *F, double a, double b, hipStream_t st);

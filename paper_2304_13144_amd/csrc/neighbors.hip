@@ -1204,7 +1204,7 @@ void build_neighbors(const mtp_model *m, const mtp_system *s, int max_nbrs, mtp_
     nb->stage_w.ensure(sizeof(int32_t) * (n > 0 ? n : 1));
     nb->rank.ensure(sizeof(int32_t) * (n > 0 ? n : 1));
     nb->runs.ensure(sizeof(uint32_t) * RUN_OFFS * (n * nt > 0 ? n * nt : 1));
-    nb->flags.ensure(sizeof(int32_t) * 8);
+    nb->flags.ensure(sizeof(StepRead));
     nb->bins_cap = bins;
     auto *geo = nb->cfg_geo.as<CfgGeo>();
     int32_t *flags = nb->flags.as<int32_t>();

@@ -293,15 +293,19 @@ __global__ void cut_gather(int64_t S, CutGeom G, const double *pos, const int32_
 }
 
 // velocity Verlet: v += h F / m (h = dt / 2 times the unit factor), then x += dt v
+// kicks = 2: the second half kick of the step before as well, whose forces
+// these are (a launch less per step)
 __global__ void md_kick_drift(int64_t n, double *x, double *v, const double *F, const int32_t *type,
-                              const double *inv_m, double h, double dt) {
+                              const double *inv_m, double h, double dt, int kicks) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const double im = inv_m[type[i]];
     for (int a = 0; a < 3; ++a) {
-        const double vi = v[3 * i + a] + h * F[3 * i + a] * im;
+        const double hf = h * F[3 * i + a];
+        double vi = fma(hf, im, v[3 * i + a]);
+        if (kicks == 2) vi = fma(hf, im, vi);
         v[3 * i + a] = vi;
-        x[3 * i + a] += dt * vi;
+        x[3 * i + a] = fma(dt, vi, x[3 * i + a]);
     }
 }
 
@@ -309,7 +313,7 @@ __global__ void md_kick(int64_t n, double *v, const double *F, const int32_t *ty
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const double im = inv_m[type[i]];
-    for (int a = 0; a < 3; ++a) v[3 * i + a] += h * F[3 * i + a] * im;
+    for (int a = 0; a < 3; ++a) v[3 * i + a] = fma(h * F[3 * i + a], im, v[3 * i + a]);
 }
 
 // Residual terms of eq. 7 for one kind of target: g = 2 w (y - t) (the
@@ -638,14 +642,17 @@ void launch_argmax(const double *g, int64_t n, double *best, int32_t *where, hip
     hipLaunchKernelGGL(argmax_kernel, dim3(1), dim3(AMAX_T), 0, st, g, n, best, where);
 }
 
-void launch_md_step(int half, int64_t n, double *x, double *v, const double *F, const int32_t *type,
-                    const double *inv_m, double h, double dt, hipStream_t st) {
+void launch_md_kick_drift(int kicks, int64_t n, double *x, double *v, const double *F, const int32_t *type,
+                          const double *inv_m, double h, double dt, hipStream_t st) {
     if (n == 0) return;
-    const dim3 grid((unsigned)((n + 255) / 256));
-    if (half == 0)
-        hipLaunchKernelGGL(md_kick_drift, grid, dim3(256), 0, st, n, x, v, F, type, inv_m, h, dt);
-    else
-        hipLaunchKernelGGL(md_kick, grid, dim3(256), 0, st, n, v, F, type, inv_m, h);
+    hipLaunchKernelGGL(md_kick_drift, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, x, v, F, type, inv_m, h, dt,
+                       kicks);
+}
+
+void launch_md_kick(int64_t n, double *v, const double *F, const int32_t *type, const double *inv_m, double h,
+                    hipStream_t st) {
+    if (n == 0) return;
+    hipLaunchKernelGGL(md_kick, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, v, F, type, inv_m, h);
 }
 
 int64_t cut_fragment(const double *pos, const int32_t *type, int64_t n, const double *H, const int *per,
