@@ -490,7 +490,7 @@ def extra_workloads(timed, passes):
                 "atom_steps_per_s": b4.n_atoms / (ms * 1e-3), "eager_ms": eager,
                 "graph_ms_per_pass": graph, "graph_passes": passes,
                 "lanes_per_neighborhood": {"moments": lanes[0], "pair_gradients": lanes[1]},
-                "step": "E, F, S, site energies (staged contraction program, no grades)"}
+                "step": "E, F, S, site energies (factorised contraction program, no grades)"}
             log(f"[bench] level 24 batch {prec}: {ms:.3f} ms/step ({b4.n_atoms / (ms * 1e-3):.4g} atom-steps/s; "
                 f"eager {eager:.3f}, graph x{passes} {graph:.3f})")
         res["batched_level24_mixed_speedup"] = (res["batched_level24_fp64"]["ms_per_step"]

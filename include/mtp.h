@@ -376,8 +376,8 @@ int mtp_profile_read(const char *kernel, double *total_ms /* host */, int64_t *l
 
 /* Autotuner: times the evaluation of this system under nine schedules --
  * 2, 4 or 8 lanes per neighborhood for the moments / contraction (4 and 8:
- * one fused launch of four or eight wavefronts per 64 neighborhoods; 2: two
- * launches) and, independently, for the pair gradients -- (HIP events:
+ * one fused launch of four or eight wavefronts per 64 neighborhoods, at level
+ * 24 eight only; 2: two launches) and, independently, for the pair gradients -- (HIP events:
  * after a warm-up, five interleaved rounds of three evaluations per
  * schedule, each schedule's minimum), keeps the fastest for this model,
  * precision and size class (floor(log2 n_atoms)) and returns it in *lanes
@@ -389,8 +389,8 @@ int mtp_profile_read(const char *kernel, double *total_ms /* host */, int64_t *l
  * staged through LDS (any m); 3: the int8 slice product (MTP_MIXED, m <=
  * 320); 4: as 1 in blocks of 32 rows, two blocks per CU (m <= 288); 5: FP64
  * MFMA with k outermost, the rows streamed in chunks of eight k steps beside
- * the products (m <= 288); 6: as 5 in chunks of two k steps, two blocks per
- * CU (m <= 288) -- keeps the fastest for this model, precision, grade mode
+ * the products (m <= 288; up to 8,192 rows in blocks of 16 or 32); 6: as 5 in
+ * chunks of two k steps, two blocks per CU (m <= 288) -- keeps the fastest for this model, precision, grade mode
  * and size class and returns it in *grade (host, nullable; 0 when no grade was
  * timed).  Every form meets the precision's error bound; they differ in
  * speed only.  Synchronises `stream`. */
