@@ -962,7 +962,8 @@ __device__ inline void wave_first(unsigned long long key, int tag, unsigned long
 // Bound by the panel's serial chain (about 1.4 us a step: search, barrier,
 // pivot row, update, one wavefront per SIMD) and the launches; one launch per
 // step that read and wrote [W | I] took 917 us at m = 212, the 28 launches
-// here 540 us.  (One block holding all of W in registers measured 485-650 us
+// here 475 us (gj_apply 8.5 us; 12.7 with its rows loaded after the pivot
+// rows' chain instead of beside it).  (One block holding all of W in registers measured 485-650 us
 // and spilled at m > 192.)
 constexpr int GJ_P = 16, GJ_T = 1024;   // columns per panel; threads of a panel block at most
 
@@ -1104,15 +1105,29 @@ __global__ __launch_bounds__(NT) void gj_panel(int m, int c0, GJBuf B) {
 }
 
 __global__ __launch_bounds__(256) void gj_apply(int m, int c0, GJBuf B) {
-    __shared__ double fp[GJ_P][GJ_P + 1];             // f of step t on the pivot row of step q
+    __shared__ double fp[GJ_P][GJ_P + 1], inv[GJ_P];  // f of step t on the pivot row of step q
     __shared__ double U[GJ_P][16], E[GJ_P][16];       // the pivot rows: as each step uses them; after the panel
-    __shared__ double fs[256][GJ_P + 1];
+    __shared__ __attribute__((aligned(16))) double fs[256][GJ_P + 2];
     static_assert(GJ_P == 16, "a block's columns are one panel's");
     const int j0 = blockIdx.x * 16;
     if (j0 == c0 || *B.singular) return;              // the panel's own columns are done
     const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4, col = j0 + tx;
     const bool on = col < m;
+    // 256 rows at a time, 16 to a thread; the first of them are in flight while the pivot rows are worked on
+    double v[16], f[16];
+    int st[16];
+    const auto load = [&](int r0) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int r = r0 + ty + 16 * i;
+            v[i] = on && r < m ? B.W[(int64_t)r * m + col] : 0.0;
+            f[i] = r < m ? B.F[(int64_t)r * GJ_P + tx] : 0.0;
+            st[i] = r < m ? B.step[r] : -1;
+        }
+    };
     const int pr = B.piv[ty];
+    load(0);
+    if (tid < GJ_P) inv[tid] = B.inv[tid];
     fp[tx][ty] = B.F[(int64_t)pr * GJ_P + tx];
     U[ty][tx] = on ? B.W[(int64_t)pr * m + col] : 0.0;
     __syncthreads();
@@ -1123,42 +1138,37 @@ __global__ __launch_bounds__(256) void gj_apply(int m, int c0, GJBuf B) {
             u[q] = U[q][tid];
 #pragma unroll
             for (int t = 0; t < q; ++t) u[q] = fma(-fp[t][q], u[t], u[q]);
-            u[q] *= B.inv[q];
+            u[q] *= inv[q];
         }
 #pragma unroll
         for (int q = 0; q < GJ_P; ++q) {
             U[q][tid] = u[q];
-            double v = u[q];
+            double w = u[q];
 #pragma unroll
-            for (int t = q + 1; t < GJ_P; ++t) v = fma(-fp[t][q], u[t], v);
-            E[q][tid] = v;
+            for (int t = q + 1; t < GJ_P; ++t) w = fma(-fp[t][q], u[t], w);
+            E[q][tid] = w;
         }
     }
-    __syncthreads();
-    double u[GJ_P];
-#pragma unroll
-    for (int q = 0; q < GJ_P; ++q) u[q] = U[q][tx];
-    for (int r0 = 0; r0 < m; r0 += 256) {   // 256 rows at a time, 16 to a thread
-        double v[16];
-        int st[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int r = r0 + ty + 16 * i;
-            v[i] = on && r < m ? B.W[(int64_t)r * m + col] : 0.0;
-            st[i] = r < m ? B.step[r] : -1;
+    for (int r0 = 0; r0 < m; r0 += 256) {
+        if (r0 > 0) {
+            load(r0);
+            __syncthreads();   // fs of the rows before is read
         }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) fs[ty + 16 * i][tx] = f[i];
         __syncthreads();
+        double u[GJ_P];
+#pragma unroll
+        for (int q = 0; q < GJ_P; ++q) u[q] = U[q][tx];
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const int r = r0 + ty + 16 * i;
-            fs[ty + 16 * i][tx] = r < m ? B.F[(int64_t)r * GJ_P + tx] : 0.0;
-        }
-        __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int r = r0 + ty + 16 * i;
-#pragma unroll
-            for (int q = 0; q < GJ_P; ++q) v[i] = fma(-fs[ty + 16 * i][q], u[q], v[i]);
+            for (int q = 0; q < GJ_P; q += 2) {
+                const double2 g = *reinterpret_cast<const double2 *>(&fs[ty + 16 * i][q]);
+                v[i] = fma(-g.x, u[q], v[i]);
+                v[i] = fma(-g.y, u[q + 1], v[i]);
+            }
             if (st[i] >= c0 && st[i] < c0 + GJ_P) v[i] = E[st[i] - c0][tx];
             if (on && r < m) B.W[(int64_t)r * m + col] = v[i];
         }
