@@ -41,9 +41,9 @@ KERNELS = ("neighbors", "efs", "efs_moments", "efs_contract", "efs_forces", "for
 TRAFFIC_KERNELS = ("efs_moments_contract<double, 16, true>", "efs_moments_contract8<double, 16, true>",
                    "efs_moments<double, 16, 8>", "efs_contract<double, 16, true>",
                    "efs_forces_fused<double, 16, 4, 2>", "efs_forces_fused<double, 16, 8, 2>",
-                   "efs_forces_rows<float, double, 16, 4>", "efs_forces_rows<float, double, 16, 8>",
+                   "efs_forces_rows<float, double, 16, 4, true>", "efs_forces_rows<float, double, 16, 8, true>",
                    "grade_f64<", "grade_f64_wide<", "grade_f64_pair<", "grade_f64_kouter<7, 8, 1>",
-                   "grade_f64_kouter<7, 2, 2>", "grade_i8<4>", "pair_search<false, 2>",
+                   "grade_f64_kouter<7, 2, 2>", "grade_i8<4>", "pair_search<(mtp::(anonymous namespace)::SearchMode)0, 2>",
                    "reverse_pairs")
 
 
@@ -395,7 +395,7 @@ def main():
                     "efs_contract": f"efs_contract<double, {level}, true>",
                     # FP64 with forces and FULL rows: the pair pass carries the rows (R = 2)
                     "efs_forces": (f"efs_forces_fused<double, {level}, {tuned[prec][1]}, 2>" if prec == "fp64" else
-                                   f"efs_forces_rows<float, double, {level}, {tuned[prec][1]}>"),
+                                   f"efs_forces_rows<float, double, {level}, {tuned[prec][1]}, true>"),
                     "grade": {"int8-slices": f"grade_i8<{(m + 63) // 64}>", "fp64-registers": "grade_f64<",
                               "fp64-lds": "grade_f64_wide<", "fp64-registers-32-row-blocks": "grade_f64_pair<",
                               "fp64-k-outer": f"grade_f64_kouter<{(m + 31) // 32}, 8, 1>",

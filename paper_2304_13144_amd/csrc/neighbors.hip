@@ -319,21 +319,24 @@ __global__ __launch_bounds__(256) void sort_bins(int32_t *flags, BinStart start,
 // Everything before the search in one block, for up to SMALL_ATOMS atoms in up
 // to SMALL_CFGS configurations: the steps of the launches above, separated by
 // barriers, with the geometry, the counters and the bins' atoms in LDS and
-// each thread's atoms in its registers.  An atom's place in its bin is the
-// number of lower indices among the bin's atoms.  Launch-bound below the line:
-// 6.2 us at 128 atoms and 7.0 at 864 against five launches of 4 to 5 us each;
-// one compute unit's throughput above it (42 us at 5,148 atoms, where the five
-// take 19 us of kernels).
-constexpr int SMALL_ATOMS = 2048, SMALL_CFGS = 64, SMALL_BINS = SMALL_ATOMS + SMALL_CFGS;
+// each thread's atoms (two, four above 2,048) in its registers.  An atom's
+// place in its bin is the number of lower indices among the bin's atoms.
+// Launch-bound below the line: 6.2 us at 128 atoms and 7.0 at 864 against five
+// launches of 4 to 5 us each; one compute unit's throughput and registers
+// above it (42 us at 5,148 atoms, where the five take 19 us of kernels).  The
+// whole build at 2,916 / 4,000 atoms: 26.5 / 30.8 us, in general launches
+// 32.8 / 34.5.
+constexpr int SMALL_ATOMS = 4096, SMALL_CFGS = 64;
+template <int PER>
 __global__ __launch_bounds__(SCAN_T) void bin_small(int n, int n_cfg, const int64_t *cfg_off, const double *cell,
                                                     const uint8_t *pbc, double rc, CfgGeo *geo_out, int32_t *flags,
                                                     int32_t *bin_count, int32_t *bin_start, int32_t *bin_atoms,
                                                     int32_t *atom_cfg, int32_t *atom_wrap, Stage S) {
+    constexpr int MAX_ATOMS = PER * SCAN_T, SMALL_BINS = MAX_ATOMS + SMALL_CFGS;
     __shared__ CfgGeo geo[SMALL_CFGS];
-    __shared__ int32_t cnt[SMALL_BINS], beg[SMALL_BINS], atoms[SMALL_ATOMS];
+    __shared__ int32_t cnt[SMALL_BINS], beg[SMALL_BINS], atoms[MAX_ATOMS];
     __shared__ int32_t wsum[SCAN_T / 64];
     const int tid = threadIdx.x, lane = tid & 63;
-    constexpr int PER = SMALL_ATOMS / SCAN_T;
     double x[PER][3];
     int t[PER];
 #pragma unroll
@@ -1214,7 +1217,7 @@ void build_neighbors(const mtp_model *m, const mtp_system *s, int max_nbrs, mtp_
              nb->stage_x.as<double>(), nb->stage_w.as<int32_t>(), nb->rank.as<int32_t>()};
     const bool small = n > 0 && n <= SMALL_ATOMS && s->n_cfg <= SMALL_CFGS;
     if (small) {
-        hipLaunchKernelGGL(bin_small, dim3(1), dim3(SCAN_T), 0, st, (int)n, s->n_cfg, s->cfg_off, s->cell, s->pbc,
+        hipLaunchKernelGGL((n <= 2 * SCAN_T ? bin_small<2> : bin_small<4>), dim3(1), dim3(SCAN_T), 0, st, (int)n, s->n_cfg, s->cfg_off, s->cell, s->pbc,
                            m->r_cut, geo, flags, nb->bin_count.as<int32_t>(), nb->bin_start.as<int32_t>(),
                            nb->bin_atoms.as<int32_t>(), nb->atom_cfg.as<int32_t>(), nb->atom_wrap.as<int32_t>(), sg);
     } else {
@@ -1239,8 +1242,10 @@ void build_neighbors(const mtp_model *m, const mtp_system *s, int max_nbrs, mtp_
     while (d2max > 0 && std::sqrt(d2max) >= m->r_cut) d2max = std::nextafter(d2max, 0.0);
     while (std::sqrt(std::nextafter(d2max, INFINITY)) < m->r_cut) d2max = std::nextafter(d2max, INFINITY);
     const Staged staged{nb->stage_x.as<double>(), nb->stage_w.as<int32_t>(), nb->bin_atoms.as<int32_t>()};
-    // blocks per bin: until there is a wavefront for every atom or two (some ten atoms a bin, 5,120 wavefronts at once)
-    const int share = small ? 2 : (n <= 16384 ? 1 : 0);
+    // 2^share blocks per bin.  More of them shorten the chain of atoms a wavefront takes and repeat the staging: of
+    // the whole build, one / two / four blocks a bin measured 23.3 / 20.5 / 19.7 us at 864 FCC atoms, 22.6 / 20.3 /
+    // 22.4 at 1,372, 26.5 / 29.5 / 34.2 at 2,916 and 51.4 / 58.8 / 72.5 at 16,384.
+    const int share = n < 1000 ? 2 : (n <= 2048 ? 1 : 0);
     auto search = [&](auto mode, auto ntc) {
         constexpr SearchMode MODE = decltype(mode)::value;
         constexpr int NTC = decltype(ntc)::value;

@@ -1,5 +1,5 @@
 """Neighbor build at the edges of its cases: one launch for everything before
-the search (up to 2048 atoms in up to 64 configurations) or the general
+the search (up to 4096 atoms in up to 64 configurations) or the general
 launches; bins that fit one window of candidates or not; more atoms in a bin
 than a run's mask holds (23); bin offsets past the run table (32, cells below
 the cut-off); atoms far outside an open cell (the float32 sieve rules nothing
@@ -73,7 +73,7 @@ def test_lists_and_reverse_pairs(name, n_types):
     assert np.abs(out["forces"].cpu().numpy() - F).max() <= 1e-10 * max(1.0, np.abs(F).max())
     # the general launches: too many atoms, too many configurations
     r = np.random.default_rng(5)
-    pos, cell = _lattice(3.3, (11, 11, 11), 0.1, r)
+    pos, cell = _lattice(3.3, (13, 13, 13), 0.1, r)
     large = synth.Config(pos, r.integers(0, n_types, len(pos)).astype(np.int32), cell)
     pos, cell = _lattice(3.3, (1, 1, 1), 0.1, r)
     few = synth.Config(pos, np.zeros(2, np.int32), cell)
@@ -87,10 +87,10 @@ def test_lists_and_reverse_pairs(name, n_types):
         assert torch.equal(f, out["forces"])
 
 
-@pytest.mark.parametrize("n", [1, 2047, 2048, 2049])
+@pytest.mark.parametrize("n", [1, 2047, 2048, 2049, 4095, 4096, 4097])
 def test_either_side_of_the_one_launch_form(n):
     r = np.random.default_rng(n)
-    pos, cell = _lattice(3.3, (11, 11, 11), 0.1, r)
+    pos, cell = _lattice(3.3, (13, 13, 13), 0.1, r)
     keep = np.sort(r.permutation(len(pos))[:n])
     c = synth.Config(pos[keep], np.zeros(n, np.int32), cell)
     m = api.Model.create(8, 1, 2.0, R_CUT)
