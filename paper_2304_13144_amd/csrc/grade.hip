@@ -1361,7 +1361,7 @@ __global__ __launch_bounds__(MV_T) void mv_swap_small(int64_t n, int m, double t
             }
         }
     }
-    if (B.st->done) return;
+    if (B.st->done) return;   // each wavefront by itself: none has met a barrier, and one that goes on stops below
     mv_wave_max(bv, bi, win);
     if (!(bv > thr)) {   // the same in every wavefront and block
         if (blockIdx.x == 0 && threadIdx.x == 0) B.st->done = 1;
@@ -1434,8 +1434,11 @@ __global__ __launch_bounds__(MV_T) void mv_swap(int64_t n, int m, double thr, in
                                                 double *cand, int32_t *swap_cand, int32_t *swap_col) {
     constexpr int RC = 8;
     __shared__ double colv[RC];
-    __shared__ int s_win;
-    if (B.st->done) return;   // written by an earlier launch, or by block 0 of this one, which stops as well
+    __shared__ int s_win, s_done;
+    // One read of `done` per block: block 0 of this launch may be writing it, and
+    // wavefronts that read it each for themselves could part ways before a barrier.
+    // In the launch that converges a block may read either value; both end here.
+    if (threadIdx.x == 0) s_done = B.st->done;
     const int par = it & 1;
     double bv = -1.0;
     int64_t bi = MV_NONE;
@@ -1453,7 +1456,7 @@ __global__ __launch_bounds__(MV_T) void mv_swap(int64_t n, int m, double thr, in
     mv_block_max(bv, bi);
     if (mine == bi && bi != MV_NONE) s_win = win;   // indices are unique: one thread
     __syncthreads();
-    if (!(bv > thr)) {
+    if (s_done || !(bv > thr)) {   // block-uniform
         if (blockIdx.x == 0 && threadIdx.x == 0) B.st->done = 1;
         return;
     }
