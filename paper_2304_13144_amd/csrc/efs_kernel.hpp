@@ -860,8 +860,10 @@ template <typename T> __device__ inline void quadratics(T x, T y, T z, T (&q)[6]
 
 // r = sqrt(d2) and 1 / r from one reciprocal square root (Goldschmidt's
 // iteration, two residual corrections of r, one of 1/r): 11 operations for
-// the 27 of a square root and a division.  d2: a squared distance, neither 0
-// nor outside the range in which its square is a normal number.
+// the 27 of a square root and a division.  d2: a squared distance whose square
+// is a normal number, or 0 (two atoms in one place, which the neighbor build
+// reports): then r is 0, so that the pair counts in the rows as it does in the
+// moments, and 1 / r is not a number, so that its force is none either.
 __device__ inline void root(double d2, double &r, double &rinv) {
     const double y = __builtin_amdgcn_rsq(d2);
     double g = d2 * y, h = 0.5 * y;
@@ -872,6 +874,7 @@ __device__ inline void root(double d2, double &r, double &rinv) {
     r = fma(fma(-g, g, d2), h, g);
     h += h;
     rinv = fma(fma(-r, h, 1.0), h, h);
+    r = d2 == 0.0 ? 0.0 : r;
 }
 
 // What an FP64 pair adds, mu by mu, so that one mu's P and gradient are live
