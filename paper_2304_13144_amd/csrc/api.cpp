@@ -344,9 +344,12 @@ void evaluate(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb, int p
         int32_t *blk = nullptr;
         const int sched = grade_sched_for(m, n, prec, o.mode);
         const int count_rows = grade_count_rows(m->act[o.mode], prec, sched, n);
+        // room for the finest counts at any size: the count's rows change with n,
+        // and the buffer must not grow (and be freed under a captured graph) when
+        // a smaller system follows a larger one
         if (want_sel)
             blk = static_cast<int32_t *>(
-                ws.get(m->selblk, sizeof(int32_t) * (size_t)((n + count_rows - 1) / count_rows + 1)));
+                ws.get(m->selblk, sizeof(int32_t) * (size_t)((n + GRADE_COUNT_MIN - 1) / GRADE_COUNT_MIN + 1)));
         {
             ProfScope ps("grade", st);
             launch_grade(m->act[o.mode], prec, brow, ldb, a.ldn, n, gam, o.argmax, st, o.sel_thr, blk, sched);

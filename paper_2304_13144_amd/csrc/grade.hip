@@ -1635,9 +1635,9 @@ int grade_count_rows(const ActiveSet &as, int precision, int sched, int64_t n) {
 
 void launch_grade(const ActiveSet &as, int precision, const double *brow, int ldb, int64_t ldn, int64_t n,
                   double *gamma, int32_t *argmax, hipStream_t st, double thr, int32_t *sel_blk, int sched) {
-    // every form counts the preselection per block of the same 64 rows
+    // the preselection is counted per block of the form: 16, 32 or 64 rows (grade_count_rows)
     static_assert(GRADE_ROWS == GF_ROWS && GRADE_ROWS == GI_ROWS, "preselection blocks are grade blocks");
-    static_assert(GRADE_ROWS % GF2_ROWS == 0, "preselection blocks");
+    static_assert(GRADE_ROWS % GF2_ROWS == 0 && GF2_ROWS >= GRADE_COUNT_MIN, "preselection blocks");
     MTP_CHECK(grade_sched_valid(as, precision, sched), MTP_E_INVAL, "grade: schedule not available for this m / precision");
     if (n == 0) return;
     MTP_CHECK(ldb >= (as.m + 31) / 32 * 32, MTP_E_INVAL, "grade: row length below the padded row length");

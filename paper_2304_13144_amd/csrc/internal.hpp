@@ -175,7 +175,10 @@ enum {
     GRADE_F64_KOUTER2 = 6
 };
 bool grade_sched_valid(const ActiveSet &as, int precision, int sched);
-// rows per preselection count the grade writes under a schedule (divides GRADE_ROWS)
+// rows per preselection count the grade writes under a schedule: 16, 32 or 64
+// (GRADE_COUNT_MIN at least; divides GRADE_ROWS).  sel_blk of launch_grade
+// holds a count for each so many rows.
+constexpr int GRADE_COUNT_MIN = 16;
 int grade_count_rows(const ActiveSet &as, int precision, int sched, int64_t n);
 void launch_grade(const ActiveSet &as, int precision, const double *brow, int ldb, int64_t ldn, int64_t n,
                   double *gamma, int32_t *argmax, hipStream_t st, double thr = 0.0, int32_t *sel_blk = nullptr,

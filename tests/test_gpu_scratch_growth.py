@@ -1,0 +1,68 @@
+"""A call that is no larger than one made before finds its scratch in place: it is
+captured without an eager run of its own, which fails if the library allocates
+(allocating under capture is an error; outside of it, growing would free what a
+captured graph still points to).  Replays equal the eager call that follows."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2304_13144_amd import api, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _model(level, n_types):
+    m = api.Model.create(level, n_types, 2.0, 5.0)
+    m.set_params(synth.theta_normal(1, n_types, m.info["n_lin"], m.info["n_rad"]))
+    k = m.m("full")
+    m.set_active_set("full", np.eye(k) + 0.1 * np.random.default_rng(k).normal(size=(k, k)) / np.sqrt(k))
+    return m
+
+
+def _lists(m, n, n_types, seed):
+    """n atoms of a displaced BCC cell with vacancies, and their lists."""
+    r = np.random.default_rng([n, seed])
+    reps = int(np.ceil((n / 2) ** (1 / 3)))
+    pos, cell = synth.lattice("bcc", 3.3, (reps, reps, reps))
+    pos = pos[np.sort(r.permutation(len(pos))[:n])] + r.normal(0.0, 0.1, (n, 3))
+    b = api.Batch([synth.Config(pos, r.integers(0, n_types, n).astype(np.int32), cell)])
+    return b, api.Neighbors().build(m, b, max_nbrs=64)
+
+
+def _buffers(b):
+    f = lambda t, *shape: torch.zeros(shape, dtype=t, device=b.device)
+    return {"energy": f(torch.float64, 1), "forces": f(torch.float64, b.n_atoms, 3),
+            "stress": f(torch.float64, 1, 3, 3), "site_e": f(torch.float64, b.n_atoms),
+            "gamma": f(torch.float64, b.n_atoms), "argmax": f(torch.int32, b.n_atoms),
+            "sel_idx": f(torch.int32, b.n_atoms), "sel_count": f(torch.int32, 1)}
+
+
+def _capture_and_check(call, out):
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call()
+    eager = None
+    for _ in range(3):
+        for t in out.values():
+            t.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        got = {k: t.clone() for k, t in out.items()}
+        if eager is None:
+            call()
+            torch.cuda.synchronize()
+            eager = {k: t.clone() for k, t in out.items()}
+        for k in out:
+            assert torch.equal(got[k], eager[k]), k
+
+
+# the preselection's counts: per 64 rows above 8,192, per 32 and per 16 rows below
+@pytest.mark.parametrize("n_large,n", [(10000, 8192), (10000, 4096), (8193, 8190)])
+def test_preselection_counts(n_large, n):
+    m = _model(8, 1)
+    large, small = _lists(m, n_large, 1, 1), _lists(m, n, 1, 2)
+    api.evaluate(m, *large, "fp64", "full", gamma_save=2.0)
+    out = _buffers(small[0])
+    _capture_and_check(lambda: api.evaluate(m, *small, "fp64", "full", out=out, gamma_save=2.0), out)
+    assert 0 < int(out["sel_count"].item())
