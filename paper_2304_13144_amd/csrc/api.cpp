@@ -54,6 +54,18 @@ int ld_of(int m, int prec) { return prec == MTP_MIXED ? (m + 63) / 64 * 64 : (m 
 // a cache line)
 int64_t ldn_of(int64_t n) { return (n + 63) / 64 * 64; }
 
+// Bytes to hold for w words of b bytes for each of n neighborhoods in padded
+// columns, wmax words being the widest that the buffer is asked for.  The
+// padding is at most 63 neighborhoods of what a call asks for; it is added for
+// the widest form, not by rounding n, so that a call with no more words than
+// one before (fewer neighborhoods of a wider form) finds its room and the
+// buffer is not freed under a captured graph.
+size_t padded_bytes(size_t b, size_t w, int64_t n, size_t wmax) {
+    return b * w * (size_t)n + sizeof(double) * wmax * 64;
+}
+// the widest rows of a model's evaluations
+size_t widest_row(const mtp_model *m) { return (size_t)ld_of(m->m_of(MTP_GRADE_FULL), MTP_MIXED); }
+
 // FULL-mode gauge: per mu drop mu+1 columns of block c_mu chosen as the
 // first mu+1 pivots of a column-pivoted Gram-Schmidt (= QR with column
 // pivoting) of the (mu+1) x (T^2 N_polyn) matrix [c_0; ...; c_mu].
@@ -267,9 +279,8 @@ void evaluate(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb, int p
         want_v ? static_cast<double *>(ws.get(m->virial, sizeof(double) * 9 * (size_t)std::max<int64_t>(1, n))) : nullptr;
     double *site = o.site_e;
     if (want_e && !site) site = static_cast<double *>(ws.get(m->sitebuf, sizeof(double) * (size_t)std::max<int64_t>(1, n)));
-    double *brow = want_rows ? static_cast<double *>(ws.get(m->brow, sizeof(double) * (size_t)ldb *
-                                                                        (size_t)std::max<int64_t>(1, ldn_of(n))))
-                             : nullptr;
+    double *brow =
+        want_rows ? static_cast<double *>(ws.get(m->brow, padded_bytes(sizeof(double), ldb, n, widest_row(m)))) : nullptr;
     if (n == 0) {
         if (o.energy) launch_zero(o.energy, sizeof(double) * s->n_cfg, st);
         if (o.stress) launch_zero(o.stress, sizeof(double) * 9 * s->n_cfg, st);
@@ -820,7 +831,7 @@ int mtp_b_rows(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb, mtp_
     MTP_HIP(hipSetDevice(m->device));
     const int mm = m->m_of(g);
     const int ldb = ld_of(mm, MTP_FP64);
-    m->brow.ensure(sizeof(double) * (size_t)ldb * (size_t)ldn_of(n_idx));
+    m->brow.ensure(padded_bytes(sizeof(double), ldb, n_idx, widest_row(m)));
     EfsArgs a{};
     a.n_atoms = n_idx;
     a.atom_list = idx;
@@ -1267,7 +1278,8 @@ int mtp_efs_backward(const mtp_model *m, const mtp_system *s, const mtp_nbrs *nb
     const size_t nc = m->basis.n_comp();
     m->dmbuf.ensure(tsz * nc * n);
     m->dtbuf.ensure(tsz * nc * n);
-    m->rows.ensure(tsz * (size_t)(m->basis.n_lin() + m->n_types * m->basis.n_rad * NPOLY) * (size_t)ldn_of(n));
+    const size_t ncol = m->basis.n_lin() + m->n_types * m->basis.n_rad * NPOLY;
+    m->rows.ensure(padded_bytes(tsz, ncol, n, ncol));
     BwdArgs b{};
     EfsArgs &a = b.e;
     a.n_atoms = n;

@@ -66,3 +66,39 @@ def test_preselection_counts(n_large, n):
     out = _buffers(small[0])
     _capture_and_check(lambda: api.evaluate(m, *small, "fp64", "full", out=out, gamma_save=2.0), out)
     assert 0 < int(out["sel_count"].item())
+
+
+# rows padded to whole blocks of 64: 80 mixed rows of 256 columns hold fewer words than 100 of 224 in FP64, and
+# 27 FULL rows of 224 columns fewer than 64 LINEAR ones of 96, though padded they are more
+@pytest.mark.parametrize("first,then", [((100, "fp64", "full"), (80, "mixed", "full")),
+                                        ((64, "fp64", "linear"), (27, "fp64", "full"))])
+def test_padded_rows(first, then):
+    m = _model(16, 2)
+    k = m.m("linear")
+    m.set_active_set("linear", np.eye(k))
+    large, small = _lists(m, first[0], 2, 1), _lists(m, then[0], 2, 2)
+    api.evaluate(m, *large, first[1], first[2], gamma_save=2.0)
+    out = _buffers(small[0])
+    _capture_and_check(lambda: api.evaluate(m, *small, then[1], then[2], out=out, gamma_save=2.0), out)
+
+
+def _backward_captured(level, first, then):
+    m = _model(level, 2)
+    large, small = _lists(m, first[0], 2, 1), _lists(m, then[0], 2, 2)
+    g = [[torch.from_numpy(np.random.default_rng(3).normal(size=s)).cuda() for s in ((1,), (b.n_atoms, 3), (1, 3, 3))]
+         for b, _ in (large, small)]
+    api.efs_backward(m, *large, *g[0], first[1])
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = api.efs_backward(m, *small, *g[1], then[1])
+    for _ in range(3):
+        got.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        seen = got.clone()
+        assert torch.equal(seen, api.efs_backward(m, *small, *g[1], then[1]))
+
+
+def test_padded_gradient_columns():   # half the neighborhoods in twice the bytes
+    _backward_captured(8, (64, "mixed"), (32, "fp64"))
