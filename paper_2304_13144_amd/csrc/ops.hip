@@ -491,7 +491,7 @@ __global__ __launch_bounds__(256) void select_write(const double *g, int64_t n, 
 // its chunk's partial theta, or straight into the result when one chunk
 // holds all neighborhoods).  The last column is xi_0: the sum of dL/dE over
 // the neighborhoods of each species.
-constexpr int CS_CHUNK = 4096;
+constexpr int CS_CHUNK = 4096, CS_ROOM = 64;
 template <typename T>
 __global__ __launch_bounds__(256) void theta_sums(const T *cols, int64_t ldn, int64_t n, int n_lin, int n_rad, int nt,
                                                   const int32_t *type, const double *gE, const int32_t *atom_cfg,
@@ -545,11 +545,11 @@ void launch_theta_sums(const void *cols, int precision, int64_t ldn, int64_t n, 
                        const double *gE, const int32_t *atom_cfg, double *out, hipStream_t st, DevBuf &work) {
     const int n_theta = nt + n_lin + n_rad * nt * nt * NPOLY, ncol = n_lin + nt * n_rad * NPOLY + 1;
     const int chunks = (int)((n + CS_CHUNK - 1) / CS_CHUNK);
-    double *dst = out;
-    if (chunks > 1) {
-        work.ensure(sizeof(double) * (size_t)chunks * n_theta);
-        dst = work.as<double>();
-    }
+    // at least CS_ROOM chunks' partials, by the first call: the next one of a few
+    // more neighborhoods finds its room (it may be captured, and growing would
+    // free what a captured graph points to)
+    work.ensure(sizeof(double) * (size_t)std::max(chunks, CS_ROOM) * n_theta);
+    double *dst = chunks > 1 ? work.as<double>() : out;
     const dim3 grid((unsigned)ncol, (unsigned)chunks);
     if (precision == MTP_FP64)
         hipLaunchKernelGGL(theta_sums<double>, grid, dim3(256), 0, st, static_cast<const double *>(cols), ldn, n, n_lin,

@@ -102,3 +102,7 @@ def _backward_captured(level, first, then):
 
 def test_padded_gradient_columns():   # half the neighborhoods in twice the bytes
     _backward_captured(8, (64, "mixed"), (32, "fp64"))
+
+
+def test_partial_gradients():   # one chunk of 4,096 neighborhoods, then two in half the bytes each
+    _backward_captured(8, (4096, "fp64"), (8192, "mixed"))
