@@ -589,7 +589,8 @@ void write_factorised(std::ostringstream &h, const Basis &B, long &flops) {
         for (int q = 0; q < nw; ++q)
             h << "  " << (q ? "else " : "") << "if constexpr (P == " << q << ") {\n" << F.emit_cluster(cl[q], cf) << "  }\n";
         h << "  }\n";
-        if (nw == 4) flops = fl + cf;
+        // counted in the form with the fewest wavefronts that runs (contract_waves in efs_kernel.hpp)
+        if (nw == (B.graphs.size() <= 128 ? 4 : 8)) flops = fl + cf;
     }
     h << "  template <typename T, typename MP>\n";
     h << "  __device__ __forceinline__ static void low_values(MP M, T *gl, T *p) {\n" << lv << "  }\n";
