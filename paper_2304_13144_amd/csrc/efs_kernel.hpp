@@ -565,8 +565,8 @@ template <typename T> __device__ inline void write_site(const EfsArgs &a, int64_
 // wavefront w evaluates the graph values of part w, all exchange them through
 // LDS (sg), each runs the (short) trie walk for V and dV/dg, and wavefront w
 // the reverse pass of part w.  The partial dV/dM are added in LDS (sdm) in a
-// fixed order.  ALIAS: sdm shares its storage with the moments M.
-template <typename T, int L, typename MA, int NW, bool ALIAS>
+// fixed order; sdm may be the storage of the moments M.
+template <typename T, int L, typename MA, int NW>
 __device__ inline void expanded_body(const EfsArgs &a, int64_t blk, const MA &M, T (*sg)[64], T (*sdm)[64]) {
     using LV = Level<L>;
     constexpr int NC = LV::NC, NG = LV::NGRAPH;
@@ -625,7 +625,7 @@ __device__ inline void expanded_body(const EfsArgs &a, int64_t blk, const MA &M,
             default: LV::template reverse_part8<7>(M, dg, dMp); break;
         }
     }
-    if constexpr (ALIAS) __syncthreads();   // every reverse part has read M
+    __syncthreads();   // every reverse part has read M
     for (int w = 0; w < NW; ++w) {
         if (wave == w) {
 #pragma unroll
@@ -657,7 +657,7 @@ __device__ __forceinline__ void contract_body(const EfsArgs &a, int64_t blk, con
     const bool live = slot < a.n_atoms;
     if constexpr (WB) constant_columns<L, NW>(a, slot, wave);
     if constexpr (expanded_program<T, L>()) {
-        expanded_body<T, L, MA, NW, true>(a, blk, M, scratch, sM);
+        expanded_body<T, L, MA, NW>(a, blk, M, scratch, sM);
     } else {
         T *dout = static_cast<T *>(a.dmbuf) + slot;
         const auto out = [&](int k, T v) {

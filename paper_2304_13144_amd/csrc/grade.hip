@@ -963,8 +963,10 @@ __device__ inline void wave_first(unsigned long long key, int tag, unsigned long
 // pivot row, update, one wavefront per SIMD) and the launches; one launch per
 // step that read and wrote [W | I] took 917 us at m = 212, the 28 launches
 // here 475 us (gj_apply 8.5 us; 12.7 with its rows loaded after the pivot
-// rows' chain instead of beside it).  (One block holding all of W in registers measured 485-650 us
-// and spilled at m > 192.)
+// rows' chain instead of beside it).  One block holding all of W in registers
+// measured 485-650 us and spilled at m > 192.  Levels 26 and 28, where built,
+// have m above 2,048 (panels of 1,024 threads with four rows each, which do
+// not fit their registers): 96 ms at m = 3,073, level 28, one species.
 constexpr int GJ_P = 16, GJ_T = 1024;   // columns per panel; threads of a panel block at most
 
 struct GJBuf {
@@ -1613,6 +1615,11 @@ bool grade_sched_valid(const ActiveSet &as, int precision, int sched) {
 constexpr int GRADE_CUS = 256;   // CUs a launch should fill
 static int grade_sched_resolve(const ActiveSet &as, int precision, int sched, int64_t n) {
     if (sched != GRADE_AUTO) return sched;
+    // mixed: the int8 product at every size.  At m = 212, call and wait included,
+    // against FP64: 37.5 and 27.8 us for 864 rows, 38.0 and 29.2 for 4,096, 38.2 and
+    // 37.3 for 5,148, 38.9 and 38.3 for 8,192, then 38.6 and 44.9 for 8,193, 88.8
+    // and 102 for 40,000.  (FP64 in blocks of 16 or 32 rows is the newer; taking it
+    // up to 8,192 rows would change the mixed form's results.)
     if (precision == MTP_MIXED && slice_product_fits(as.m)) return GRADE_I8;
     // k-outer: one block of 64 rows per CU with the long chunks, two per CU
     // beyond (m = 212: 16,384 rows 29.8 against 30.2 us, 65,536 rows 118 against

@@ -924,11 +924,10 @@ __device__ inline void lds_barrier() {
 constexpr int SEARCH_GRID = 8192;   // blocks at most (a bin each or several: the host knows only a bound on the bins)
 enum SearchMode { NARROW, WIDE, BOTH };
 template <SearchMode MODE, int NT>
-__global__ __launch_bounds__(256, MODE == NARROW ? 5 : 2) void pair_search(int n_cfg, int share, int max_nbrs, double rc, double d2max,
-                                                   const CfgGeo *geo, Staged S, BinStart bin_start,
-                                                   const int32_t *bin_count, int32_t *tcnt, double *rout,
-                                                   int32_t *jout, int32_t *shout, int32_t *flags,
-                                                   int32_t *wide_list, unsigned *runs_out) {
+__global__ __launch_bounds__(256, MODE == NARROW ? 5 : 2)
+void pair_search(int n_cfg, int share, int max_nbrs, double rc, double d2max, const CfgGeo *geo, Staged S,
+                 BinStart bin_start, const int32_t *bin_count, int32_t *tcnt, double *rout, int32_t *jout,
+                 int32_t *shout, int32_t *flags, int32_t *wide_list, unsigned *runs_out) {
     __shared__ Window W;
     __shared__ Sieve F;
     __shared__ Runs<NT> runs[4];
@@ -1217,9 +1216,10 @@ void build_neighbors(const mtp_model *m, const mtp_system *s, int max_nbrs, mtp_
              nb->stage_x.as<double>(), nb->stage_w.as<int32_t>(), nb->rank.as<int32_t>()};
     const bool small = n > 0 && n <= SMALL_ATOMS && s->n_cfg <= SMALL_CFGS;
     if (small) {
-        hipLaunchKernelGGL((n <= 2 * SCAN_T ? bin_small<2> : bin_small<4>), dim3(1), dim3(SCAN_T), 0, st, (int)n, s->n_cfg, s->cfg_off, s->cell, s->pbc,
-                           m->r_cut, geo, flags, nb->bin_count.as<int32_t>(), nb->bin_start.as<int32_t>(),
-                           nb->bin_atoms.as<int32_t>(), nb->atom_cfg.as<int32_t>(), nb->atom_wrap.as<int32_t>(), sg);
+        hipLaunchKernelGGL((n <= 2 * SCAN_T ? bin_small<2> : bin_small<4>), dim3(1), dim3(SCAN_T), 0, st, (int)n,
+                           s->n_cfg, s->cfg_off, s->cell, s->pbc, m->r_cut, geo, flags, nb->bin_count.as<int32_t>(),
+                           nb->bin_start.as<int32_t>(), nb->bin_atoms.as<int32_t>(), nb->atom_cfg.as<int32_t>(),
+                           nb->atom_wrap.as<int32_t>(), sg);
     } else {
         hipLaunchKernelGGL(nbr_prepare, dim3((unsigned)std::min<int64_t>((bins + SCAN_T - 1) / SCAN_T, 512) + 1),
                            dim3(SCAN_T), 0, st, s->n_cfg, s->cfg_off, s->cell, s->pbc, m->r_cut, geo, flags,
@@ -1249,11 +1249,11 @@ void build_neighbors(const mtp_model *m, const mtp_system *s, int max_nbrs, mtp_
     auto search = [&](auto mode, auto ntc) {
         constexpr SearchMode MODE = decltype(mode)::value;
         constexpr int NTC = decltype(ntc)::value;
-        hipLaunchKernelGGL((pair_search<MODE, NTC>), dim3((unsigned)std::min<int64_t>(bins << share, MODE == WIDE ? 512 : SEARCH_GRID)),
-                           dim3(TB), 0, st, s->n_cfg, share, max_nbrs, m->r_cut, d2max, geo, staged, bstart,
-                           nb->bin_count.as<int32_t>(), nb->tcnt.as<int32_t>(), nb->r.as<double>(),
-                           nb->j.as<int32_t>(), nb->shift.as<int32_t>(), flags, nb->bin_cursor.as<int32_t>(),
-                           nb->runs.as<uint32_t>());
+        const dim3 grid((unsigned)std::min<int64_t>(bins << share, MODE == WIDE ? 512 : SEARCH_GRID));
+        hipLaunchKernelGGL((pair_search<MODE, NTC>), grid, dim3(TB), 0, st, s->n_cfg, share, max_nbrs, m->r_cut, d2max,
+                           geo, staged, bstart, nb->bin_count.as<int32_t>(), nb->tcnt.as<int32_t>(),
+                           nb->r.as<double>(), nb->j.as<int32_t>(), nb->shift.as<int32_t>(), flags,
+                           nb->bin_cursor.as<int32_t>(), nb->runs.as<uint32_t>());
     };
     auto all = [&](auto ntc) {
         if (small) {

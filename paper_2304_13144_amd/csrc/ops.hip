@@ -634,8 +634,8 @@ void launch_cfg_rows(const double *rows, int64_t ldn, int ldb, int64_t n, const 
     if (s->n_cfg <= 0) return;
     const unsigned nch = (unsigned)((n + ROW_CHUNK - 1) / ROW_CHUNK), tiles = (unsigned)((ldb + ROW_COLS - 1) / ROW_COLS);
     if (nch) hipLaunchKernelGGL(row_partials, dim3(nch, tiles), dim3(256), 0, st, rows, ldn, ldb, n, (int64_t)nch, part);
-    hipLaunchKernelGGL(row_final, dim3((unsigned)((s->n_cfg + ROW_CFGS - 1) / ROW_CFGS), tiles), dim3(256), 0, st, rows, ldn, ldb, (int64_t)nch, part,
-                       s->cfg_off, s->n_cfg, out);
+    const dim3 grid((unsigned)((s->n_cfg + ROW_CFGS - 1) / ROW_CFGS), tiles);
+    hipLaunchKernelGGL(row_final, grid, dim3(256), 0, st, rows, ldn, ldb, (int64_t)nch, part, s->cfg_off, s->n_cfg, out);
 }
 
 void launch_argmax(const double *g, int64_t n, double *best, int32_t *where, hipStream_t st) {
