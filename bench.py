@@ -51,23 +51,34 @@ def log(msg):
     print(msg, file=sys.stderr, flush=True)
 
 
-def efs_flops_per_atom(n_pairs_per_atom, nc, nr, contraction_flops, with_rows, fused_rows=True):
-    """Algorithmic flops per neighborhood of the evaluation kernels.
+def mu_components(level, nr):
+    """Moment components per radial function mu: tensors of degree 0 to min(3, (level - 4 - 4 mu) / 2)."""
+    size = (1, 4, 10, 20)
+    return [size[min(3, (level - 4 - 4 * mu) // 2)] for mu in range(nr)]
+
+
+def efs_flops_per_atom(n_pairs_per_atom, level, nc, nr, contraction_flops, with_rows, fp64=True):
+    """Flops per neighborhood of the evaluation kernels, as they run (an FMA is two).
 
     efs_moments, per pair:  r (6) + T_0..T_7 (12) + f_mu (16 nr + 2) + monomials (16) + moments (2 nc)
-    efs_contract:           the generated contraction program (graph values, trie walk, reverse)
+    efs_contract:           the generated contraction program
     efs_forces, per pair:
-      pair gradients:       r (6) + T, T' (30) + f, f' (32 nr + 4 nr + 3) + monomials (16)
-                            + P and grad P (8 nc) + g assembly (8 nr + 7) + virial (18)
-      b-row c part, in the same pass (FP64, fused_rows): T_beta cut (NPOLY) + 2 nr NPOLY --
-                            P and the Chebyshev values are the gradient's;
-      in row blocks of their own (the mixed form, whose rows are FP64 and its
-      pair gradients FP32): r (6) + T (12) + cutoff (3) + monomials (16) + P (2 nc)
-                            + 2 nr NPOLY + NPOLY
+      pair gradients:       r (6) + T, T' (30) + f, f' (32 nr + 4 nr + 3) + P and grad P + g assembly (8 nr + 7)
+                            + virial (18); P and grad P in FP64 from the symmetric tensors: second-degree
+                            products (9) + per mu of 1, 4, 10 or 20 components 0, 6, 30 or 72; in FP32 from
+                            monomials (16 + 8 nc)
+      b-row c part, in the same pass (FP64): T_beta cut (NPOLY) + 2 nr NPOLY -- P and the Chebyshev values
+                            are the gradient's;
+      in row blocks of their own (the mixed form, whose rows are FP64): r (6) + T (12) + cutoff (3)
+                            + second-degree products (9) + P alone (per mu 0, 6, 24 or 60) + 2 nr NPOLY + NPOLY
     """
+    mu = mu_components(level, nr)
+    assert sum(mu) == nc, (mu, nc)
     p1 = 6 + 12 + 16 * nr + 2 + 16 + 2 * nc
-    p3 = 6 + 30 + 36 * nr + 3 + 16 + 8 * nc + 8 * nr + 7 + 18
-    p4 = 8 + 2 * nr * 8 if fused_rows else 6 + 12 + 3 + 16 + 2 * nc + 2 * nr * 8 + 8
+    grad = 9 + sum({1: 0, 4: 6, 10: 30, 20: 72}[n] for n in mu) if fp64 else 16 + 8 * nc
+    p3 = 6 + 30 + 36 * nr + 3 + grad + 8 * nr + 7 + 18
+    p4 = 8 + 2 * nr * 8 if fp64 else \
+        6 + 12 + 3 + 9 + sum({1: 0, 4: 6, 10: 24, 20: 60}[n] for n in mu) + 2 * nr * 8 + 8
     return {"efs_moments": n_pairs_per_atom * p1, "efs_contract": float(contraction_flops),
             "efs_forces": n_pairs_per_atom * (p3 + (p4 if with_rows else 0))}
 
@@ -345,8 +356,8 @@ def main():
     prec = a.precision
     r = results[prec]
     m = info["m_full"]
-    fl = efs_flops_per_atom(pairs_per_atom, info["n_comp"], info["n_rad"], info["contraction_flops"], True,
-                            fused_rows=prec == "fp64")
+    fl = efs_flops_per_atom(pairs_per_atom, level, info["n_comp"], info["n_rad"], info["contraction_flops"], True,
+                            fp64=prec == "fp64")
     if r["kernels"]["efs_contract"]["launches"] == 0:   # four lanes: moments and contraction in one launch
         fl = {"efs_moments_contract": fl["efs_moments"] + fl["efs_contract"], "efs_forces": fl["efs_forces"]}
     per_kernel = {}
