@@ -226,10 +226,10 @@ __global__ void fill_bins(int64_t n, const int32_t *atom_bin, const int32_t *ato
 }
 
 __device__ inline int pack_q(int x, int y, int z) { return (x + 512) | ((y + 512) << 10) | ((z + 512) << 20); }
-// the same modulo 1024 a field, of numbers of any size
-__device__ inline int pack_any(int x, int y, int z) {
-    return ((x + 512) & 1023) | ((y + 512) & 1023) << 10 | ((z + 512) & 1023) << 20;
-}
+// An atom's image number as it is packed: far ones (reported as too far from 255 on) end where the field still
+// holds the sum with the wrap of any bin of a one-window search (at most 32: 64 bin offsets), which would otherwise
+// carry into the next field or into the species above them.
+__device__ inline int near_image(int w) { return w < -478 ? -478 : (w > 478 ? 478 : w); }
 
 struct Stage {
     const double *pos;
@@ -237,7 +237,7 @@ struct Stage {
     const CfgGeo *geo;
     int n_types;
     double *sx;     // [3 n] x_j - w_j.H
-    int32_t *sw;    // [n] pack_any(-w_j) | species << 30 (0 where out of range: that is reported)
+    int32_t *sw;    // [n] pack_q(-w_j) | species << 30 (0 where out of range: that is reported)
     int32_t *rank;  // [n] by atom: its place within its bin
 };
 
@@ -250,7 +250,7 @@ __device__ inline void stage_at(const Stage &S, int64_t u, const double (&x)[3],
     if (w[0] < -255 || w[0] > 255 || w[1] < -255 || w[1] > 255 || w[2] < -255 || w[2] > 255) wide = true;
     const bool out = t < 0 || t >= S.n_types;
     if (out) bad = true;   // reported as an error; 0 keeps later indexing in range
-    S.sw[u] = pack_any(-w[0], -w[1], -w[2]) | (out ? 0 : t) << 30;
+    S.sw[u] = pack_q(-near_image(w[0]), -near_image(w[1]), -near_image(w[2])) | (out ? 0 : t) << 30;
 }
 __device__ inline void stage_atom(const Stage &S, int64_t u, int64_t j, bool &wide, bool &bad) {
     const double x[3] = {S.pos[3 * j], S.pos[3 * j + 1], S.pos[3 * j + 2]};
@@ -442,8 +442,7 @@ __device__ inline int rank_in(unsigned long long m) {
 __device__ inline int field(int p, int k) { return ((p >> (10 * k)) & 1023) - 512; }
 
 constexpr int NO_WRAP = 512 | 512 << 10 | 512 << 20;   // pack_q(0, 0, 0); x + pack_q(q) - NO_WRAP adds q to packed x
-// q added to the packed -w_j of a staged word, its species kept whatever the sum (a shift that does not fit is
-// reported, and the list is still grouped by species)
+// the same where q may be of any size (cells far below the cut-off): the species above the fields is kept
 __device__ inline int add_wrap(int sw, int q) {
     return (int)(((unsigned)sw & 0xc0000000u) | ((unsigned)(sw + (q - NO_WRAP)) & 0x3fffffffu));
 }
@@ -617,7 +616,7 @@ __device__ inline void stage_sieve(Window &W, Sieve &F, const Around &A, int n_o
         if (e < A.total) {
             const double y[3] = {S.sx[3 * u], S.sx[3 * u + 1], S.sx[3 * u + 2]};
             const int j = S.bin_atoms[u];
-            const int qt = add_wrap(S.sw[u], q);
+            const int qt = S.sw[u] + (q - NO_WRAP);
             double d[3] = {y[0] - o[0], y[1] - o[1], y[2] - o[2]};
             if (wraps) {
                 const int qx = field(q, 0), qy = field(q, 1), qz = field(q, 2);
